@@ -27,6 +27,11 @@ FLAGS = [
     # statements, so that a function inlined into different kernels rounds the
     # same way in each (the schedulers must give bit-identical results)
     "-ffp-contract=on",
+    # the machine-level loop-invariant pass hoists the literals of the double-precision
+    # polynomials (pow, ln, exp) out of the particle loops into vector registers, which
+    # cost the streaming passes up to half of their waves: k_prepass<float> takes 70
+    # instead of 128 registers without it, k_lepton<float> 119 instead of 172
+    "-mllvm", "-disable-machine-licm",
     "-Wall", "-Wno-unused-function",
 ]
 

@@ -510,8 +510,13 @@ qed_status step_impl(qed_ctx *c, qed_particles *p, const qed_field fields[3], do
     if (r == hipSuccess && emission && !binned)
         r = launch(c, tiled ? qed::K_TILED : qed::K_LEPTON, a, prec, lepton_blocks);
     if (binned) {
-        if (r == hipSuccess)
-            r = launch(c, qed::K_PREPASS, a, prec, grid_for(lep_cap, c->num_cu * (int)c->tune.prepass_blocks_per_cu));
+        // a grid between one and two times what the chip holds would leave the blocks of
+        // its second round alone on it (16.8M electrons at 7 resident blocks per CU: a
+        // grid of 8 took 473 us, one of 7 403)
+        uint32_t pb = c->tune.prepass_blocks_per_cu;
+        const uint32_t held = (uint32_t)qed::kPrepassBlocks[surrogate ? 1 : 0];
+        if (prec == 1 && pb > held && pb < 2 * held) pb = held;
+        if (r == hipSuccess) r = launch(c, qed::K_PREPASS, a, prec, grid_for(lep_cap, c->num_cu * (int)pb));
         if (r == hipSuccess) r = launch(c, qed::K_SCAN, a, prec, 1);
         if (r == hipSuccess)
             r = launch(c, qed::K_SCATTER, a, prec, grid_for(lep_cap, c->num_cu * (int)c->tune.scatter_blocks_per_cu));

@@ -154,6 +154,11 @@ enum KernelId {
     K_COUNT
 };
 
+// Blocks of k_prepass<float> that one compute unit holds at a time, without and with the
+// optical-depth path (more than 6 there squeeze its scalar registers: 430 to 450 us for
+// 16.8M electrons).
+constexpr int kPrepassBlocks[2] = {8, 6};
+
 // Enqueue one kernel of a step (precision: 0 = F64, 1 = MIXED).  blocks is the
 // grid size in x; lepton kernels add y = 2 (one row per lepton species).
 hipError_t launch_kernel(int id, const StepArgs &a, int precision, int blocks, hipStream_t s);

@@ -35,6 +35,7 @@
 // evaluated in double at the step start.
 #include <type_traits>
 
+#include "qed_accept.hpp"
 #include "qed_device.hpp"
 #include "qed_internal.hpp"
 #include "qed_mlp.hpp"
@@ -87,6 +88,12 @@ __device__ __forceinline__ bool photon_quiet(double chi, double eps, double st) 
 __device__ __forceinline__ u64 lanemask_lt() {
     const int l = __lane_id();
     return (1ull << l) - 1ull;
+}
+
+// The first active lane's value, in scalar registers.
+__device__ __forceinline__ u64 first_lane(u64 v) {
+    return ((u64)__builtin_amdgcn_readfirstlane((uint32_t)(v >> 32)) << 32) |
+           __builtin_amdgcn_readfirstlane((uint32_t)v);
 }
 
 template <class T>
@@ -189,32 +196,100 @@ __device__ __forceinline__ void flush_tally(const Tally<R> &t, DevState *st, int
     flush_tallies<R, 1>(&t, w, st, species);
 }
 
-// Children of one wave staged in LDS and written out with one atomic per flush.
-// A child's id (a Philox block of its parent's id and counter) is formed when the
-// buffer is written out, by all the flushing lanes together, rather than by the
-// few lanes that emit in one sub-step.
-// Every flush is an atomic on the one counter of the species that all waves of the
-// chip share.  TB: with birth times.  The optical-depth path (TB false: it runs no
-// cascades) emits its photons about twice as fast as Algorithm 1's loop in a hot
-// spot, and waits on those atomics, so its buffer holds 128 children (each atomic
-// then covers twice the writes; 52 bytes of LDS per entry); the plain path's 64
-// entries keep its LDS small at no measurable cost.
-template <class R, bool TB = true>
-struct ChildBuf {
-    static constexpr uint32_t kCap = TB ? 64 : 128;
-    double x[kCap], y[kCap], z[kCap];
-    R px[kCap], py[kCap], pz[kCap], w[kCap];
-    uint64_t parent[kCap];
-    uint32_t ctr[kCap];        // the id's counter word (the event's index)
-    double tb[TB ? kCap : 1];  // birth time within the step
+// Children staged in LDS.  A child's id (a Philox block of its parent's id and counter)
+// is formed when it is written out, by all the writing lanes together, rather than by
+// the few lanes that emit in one sub-step.  TB: with birth times (the optical-depth
+// path runs no cascades).
+template <class R, uint32_t CAP, bool TB>
+struct Children {
+    double x[CAP], y[CAP], z[CAP];
+    R px[CAP], py[CAP], pz[CAP], w[CAP];
+    uint64_t parent[CAP];
+    uint32_t ctr[CAP];        // the id's counter word (the event's index)
+    double tb[TB ? CAP : 1];  // birth time within the step
+};
+
+// A pointer of the species.  LAZY: it lies in LDS and is read where it is used, where a
+// dozen pointers held through the sub-step loops would cost their registers.
+template <bool LAZY, class T>
+__device__ __forceinline__ T *dst_ptr(T *const &p) {
+    if constexpr (LAZY) return *(T *const volatile *)&p;
+    return p;
+}
+
+// Entry e of c to its slot.
+template <bool LAZY, class R, uint32_t CAP, bool TB>
+__device__ __forceinline__ void store_child(const Children<R, CAP, TB> &c, uint32_t e, const SpeciesDev &dst, u64 slot,
+                                            uint64_t seed, uint32_t step) {
+    if (slot >= dst.cap) return;
+    dst_ptr<LAZY>(dst.x)[slot] = c.x[e];
+    dst_ptr<LAZY>(dst.y)[slot] = c.y[e];
+    dst_ptr<LAZY>(dst.z)[slot] = c.z[e];
+    ((R *)dst_ptr<LAZY>(dst.ux))[slot] = c.px[e];
+    ((R *)dst_ptr<LAZY>(dst.uy))[slot] = c.py[e];
+    ((R *)dst_ptr<LAZY>(dst.uz))[slot] = c.pz[e];
+    ((R *)dst_ptr<LAZY>(dst.w))[slot] = c.w[e];
+    dst_ptr<LAZY>(dst.id)[slot] = child_id(seed, c.parent[e], step, c.ctr[e], 0);
+    if (uint64_t *q = dst_ptr<LAZY>(dst.parent)) q[slot] = c.parent[e];
+    if constexpr (TB)
+        if (double *q = dst_ptr<LAZY>(dst.birth)) q[slot] = c.tb[e];
+    if (double *q = dst_ptr<LAZY>(dst.tau)) q[slot] = -1.0;
+}
+
+// Algorithm 1: one pool per block, in two halves of kSeg entries, written out a half at a
+// time with one atomic on the species' counter.  All waves of the chip share that
+// counter, and atomics on one address are served one after another, 12 ns each (measured
+// from 1,024 to 4,096 waves): with a 64-entry buffer per wave the 4.9 million photons of
+// the 16.8M-electron hot spot took 77,000 of them, 0.9 of the heavy queue's 1.40 ms;
+// with the pool it takes 1.24.
+//
+// A wave takes its entries from tail, writes them and adds their number to the half's
+// written; the wave that completes a half writes it out and frees it (freed: how often
+// each half has been).  Filling f of the block (entries f kSeg .. (f + 1) kSeg - 1) uses
+// half f & 1 and starts when filling f - 2 has been written out.  A wave that must wait
+// for that holds up nobody: the oldest filling not yet written out has its half free, so
+// its entries are written by waves that do not wait, and the last of these writes it out
+// without waiting for another wave.
+template <class R>
+struct ChildPool : Children<R, 448, true> {
+    static constexpr uint32_t kSeg = 224;
+    uint32_t tail, written[2], freed[2];
+    SpeciesDev dst;
+};
+
+// The optical-depth path: one buffer per wave.  Its loop resolves smaller batches than
+// Algorithm 1's, and the pool's exchange between waves at each of them cost it 2% in the
+// hot spot and 8% at 300,000 electrons.
+struct ChildBuf : Children<float, 128, false> {
+    static constexpr uint32_t kCap = 128;
     uint32_t count;
 };
 
-// Write the staged children to the species' tail.  Called by the active lanes of
-// a wave (any subset); they share the writes.
-template <class R, bool TB>
-__device__ __forceinline__ void flush_children(ChildBuf<R, TB> &cb, const SpeciesDev &dst, uint64_t seed,
-                                               uint32_t step) {
+// Write out and free a complete half.  Called by the active lanes of one wave (any
+// subset); they share the writes.
+template <class R>
+__device__ __forceinline__ void flush_half(ChildPool<R> &cb, uint32_t half, uint64_t seed, uint32_t step) {
+    constexpr uint32_t kSeg = ChildPool<R>::kSeg;
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    const u64 exec = __ballot(1);
+    const int leader = __ffsll((long long)exec) - 1;
+    const uint32_t nact = (uint32_t)__popcll(exec);
+    const uint32_t me = (uint32_t)__popcll(exec & lanemask_lt());
+    u64 base = 0;
+    if (__lane_id() == leader) base = atomicAdd(dst_ptr<true>(cb.dst.n), (u64)kSeg);
+    base = __shfl(base, leader);
+    for (uint32_t e = me; e < kSeg; e += nact) store_child<true>(cb, half * kSeg + e, cb.dst, base + e, seed, step);
+    __syncwarp();
+    if (__lane_id() == leader) {
+        cb.written[half] = 0;
+        __hip_atomic_fetch_add(&cb.freed[half], 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+    __syncwarp();
+}
+
+// Write the wave's staged children to the species' tail.  Called by the active lanes of
+// the wave (any subset); they share the writes.
+__device__ __forceinline__ void flush_children(ChildBuf &cb, const SpeciesDev &dst, uint64_t seed, uint32_t step) {
     __syncwarp();
     const uint32_t n = cb.count;
     if (n == 0) return;
@@ -225,23 +300,7 @@ __device__ __forceinline__ void flush_children(ChildBuf<R, TB> &cb, const Specie
     u64 base = 0;
     if (__lane_id() == leader) base = atomicAdd(dst.n, (u64)n);
     base = __shfl(base, leader);
-    for (uint32_t e = me; e < n; e += nact) {
-        const u64 slot = base + e;
-        if (slot < dst.cap) {
-            dst.x[slot] = cb.x[e];
-            dst.y[slot] = cb.y[e];
-            dst.z[slot] = cb.z[e];
-            ((R *)dst.ux)[slot] = cb.px[e];
-            ((R *)dst.uy)[slot] = cb.py[e];
-            ((R *)dst.uz)[slot] = cb.pz[e];
-            ((R *)dst.w)[slot] = cb.w[e];
-            dst.id[slot] = child_id(seed, cb.parent[e], step, cb.ctr[e], 0);
-            if (dst.parent) dst.parent[slot] = cb.parent[e];
-            if constexpr (TB)
-                if (dst.birth) dst.birth[slot] = cb.tb[e];
-            if (dst.tau) dst.tau[slot] = -1.0;
-        }
-    }
+    for (uint32_t e = me; e < n; e += nact) store_child<false>(cb, e, dst, base + e, seed, step);
     __syncwarp();
     cb.count = 0;
     __syncwarp();
@@ -256,22 +315,46 @@ struct Draw;
 template <>
 struct Draw<float> {
     u32x4 w;
-    __device__ __forceinline__ void get(uint32_t k, uint32_t idlo, uint32_t idhi, uint32_t step,
-                                        uint32_t klo, uint32_t khi, float &x, float &y) {
-        if ((k & 1u) == 0u) w = philox10(idlo, idhi, step, k >> 1, klo, khi);
+    static constexpr float kYScale = 0x1p+24f;   // test() over y
+    // the block that holds sub-step k
+    __device__ __forceinline__ void block(uint32_t k, uint32_t idlo, uint32_t idhi, uint32_t step, uint32_t klo,
+                                          uint32_t khi) {
+        w = philox10(idlo, idhi, step, k >> 1, klo, khi);
+    }
+    // of its first (half = 0) or second pair: the word of x, and y in units of 2^-24
+    __device__ __forceinline__ uint32_t xword(int half) const { return half ? w.z : w.x; }
+    __device__ __forceinline__ float test(int half) const { return (float)(((half ? w.w : w.y) >> 8) | 1u); }
+    // the pair of sub-step k
+    __device__ __forceinline__ void pair(uint32_t k, float &x, float &y) const {
         const bool odd = (k & 1u) != 0u;
         x = u24(odd ? w.z : w.x);
         y = u24(odd ? w.w : w.y);
+    }
+    __device__ __forceinline__ void get(uint32_t k, uint32_t idlo, uint32_t idhi, uint32_t step,
+                                        uint32_t klo, uint32_t khi, float &x, float &y) {
+        if ((k & 1u) == 0u) block(k, idlo, idhi, step, klo, khi);
+        pair(k, x, y);
     }
 };
 
 template <>
 struct Draw<double> {
-    __device__ __forceinline__ void get(uint32_t k, uint32_t idlo, uint32_t idhi, uint32_t step,
-                                        uint32_t klo, uint32_t khi, double &x, double &y) {
-        const u32x4 w = philox10(idlo, idhi, step, k, klo, khi);
+    u32x4 w;
+    static constexpr double kYScale = 1.0;
+    __device__ __forceinline__ void block(uint32_t k, uint32_t idlo, uint32_t idhi, uint32_t step, uint32_t klo,
+                                          uint32_t khi) {
+        w = philox10(idlo, idhi, step, k, klo, khi);
+    }
+    __device__ __forceinline__ uint32_t xword(int) const { return w.x; }
+    __device__ __forceinline__ double test(int) const { return u53(w.z, w.w); }
+    __device__ __forceinline__ void pair(uint32_t, double &x, double &y) const {
         x = u53(w.x, w.y);
         y = u53(w.z, w.w);
+    }
+    __device__ __forceinline__ void get(uint32_t k, uint32_t idlo, uint32_t idhi, uint32_t step,
+                                        uint32_t klo, uint32_t khi, double &x, double &y) {
+        block(k, idlo, idhi, step, klo, khi);
+        pair(k, x, y);
     }
 };
 
@@ -365,7 +448,9 @@ __device__ __forceinline__ uint32_t lepton_nsub_own(const StepArgs &a, const Lep
     const double gd = sqrt(1.0 + (double)p.ux * p.ux + (double)p.uy * p.uy + (double)p.uz * p.uz);
     const double chi0 = chi_def(gd, p.ux, p.uy, p.uz, p.ex, p.ey, p.ez, p.bx, p.by, p.bz);
     bool capped;
-    const uint32_t N = nsub(bound_emission(chi0, gd, dt), a.p_max_lep, a.max_sub, &capped);
+    uint32_t cap = a.max_sub;
+    asm volatile("" : "+s"(cap));   // its double is formed here, not held across the particle loop
+    const uint32_t N = nsub(bound_emission(chi0, gd, dt), a.p_max_lep, cap, &capped);
     tl.capped += capped;
     return N;
 }
@@ -379,117 +464,191 @@ __device__ __forceinline__ uint32_t lepton_nsub(const StepArgs &a, int s, u64 i,
 }
 
 // Photon emission of the accepting lanes (acc; m = their ballot): the photon of
-// energy fraction delta = x3 along u is staged in the wave's LDS buffer with the
+// energy fraction delta = x3 along u is staged in LDS with the
 // parent's position and weight, and the parent recoils to gamma' = (1 - delta)
 // gamma in the same direction.  Called by every lane of the wave that is still in
-// the sub-step loop.  k: the sub-step (birth time t0 + (k + 1) st); ctr: the
+// the sub-step loop.  k: the sub-step (of N; birth time t0 + (k + 1) st); ctr: the
 // counter of the photon's id (the sub-step in Algorithm 1, the emission's index in
 // the step for the surrogate, which can emit more than once in a sub-step).
-// A lepton's position and weight at the start of the step, held for its emissions
+// A lepton's position, weight and id at the start of the step, held for its emissions
 // and its end-of-step position (the step does not change them in memory).
 template <class R>
 struct Origin {
     double x, y, z;
     R w;
+    uint64_t id;
 };
 
 template <class R>
 __device__ __forceinline__ Origin<R> origin_of(const SpeciesDev &sp, u64 i) {
-    return Origin<R>{sp.x[i], sp.y[i], sp.z[i], ((const R *)sp.w)[i]};
+    return Origin<R>{sp.x[i], sp.y[i], sp.z[i], ((const R *)sp.w)[i], sp.id[i]};
 }
 
-template <class R, bool TB>
-__device__ __forceinline__ void stage_emission(const StepArgs &a, const Origin<R> &org, uint64_t pid,
-                                               uint32_t ctr, uint32_t k, bool acc, u64 m, R x3, R omx3, R g,
-                                               R u2, R dx,
-                                               R dy, R dz, R &ux, R &uy, R &uz, ChildBuf<R, TB> &cb,
-                                               uint32_t &nev, double t0, double st, uint32_t step) {
+// Where Algorithm 1's loop holds it: the float kernels in LDS, which keeps them at four
+// waves per SIMD without spilling (a spilled origin was reloaded behind the wave's other
+// memory traffic at every emission, some 4 us each time), the double ones in registers.
+template <class R>
+struct OriginHold {
+    __device__ __forceinline__ void put(const Origin<R> &o, Origin<R> &reg) { reg = o; }
+    __device__ __forceinline__ Origin<R> get(const Origin<R> &reg) const { return reg; }
+};
+template <>
+struct OriginHold<float> {
+    double x[kBlock], y[kBlock], z[kBlock];
+    uint64_t id[kBlock];
+    float w[kBlock];
+    __device__ __forceinline__ void put(const Origin<float> &o, Origin<float> &) {
+        x[threadIdx.x] = o.x;
+        y[threadIdx.x] = o.y;
+        z[threadIdx.x] = o.z;
+        w[threadIdx.x] = o.w;
+        id[threadIdx.x] = o.id;
+    }
+    __device__ __forceinline__ Origin<float> get(const Origin<float> &) const {
+        return Origin<float>{x[threadIdx.x], y[threadIdx.x], z[threadIdx.x], w[threadIdx.x], id[threadIdx.x]};
+    }
+};
+
+template <class R>
+struct Emission {
+    bool acc;
+    uint32_t ctr, k;
+    R x3, omx3, g, u2, inv;  // delta, 1 - delta, gamma, |u|^2, 1 / |u|
+    R dx, dy, dz;            // displacement since the step start
+};
+
+template <class R, uint32_t CAP, bool TB>
+__device__ __forceinline__ void put_child(Children<R, CAP, TB> &c, uint32_t e, const Origin<R> &org,
+                                          const Emission<R> &em, R ux, R uy, R uz) {
+    const R eph = em.x3 * em.g * em.inv;
+    c.x[e] = org.x + (double)em.dx;
+    c.y[e] = org.y + (double)em.dy;
+    c.z[e] = org.z + (double)em.dz;
+    c.px[e] = ux * eph;
+    c.py[e] = uy * eph;
+    c.pz[e] = uz * eph;
+    c.w[e] = org.w;
+    c.ctr[e] = em.ctr;
+    c.parent[e] = org.id;
+}
+
+// gamma' = (1 - delta) gamma, same direction
+template <class R>
+__device__ __forceinline__ void recoil(const Emission<R> &em, R &ux, R &uy, R &uz) {
+    const R g1 = em.omx3 * em.g;
+    const R u1 = sqrt_(fmax(g1 * g1 - R(1), R(0)));
+    const R sc = u1 * em.inv;
+    ux *= sc;
+    uy *= sc;
+    uz *= sc;
+}
+
+template <class R>
+__device__ __forceinline__ void stage_emission(const StepArgs &a, const Origin<R> &org, Emission<R> &em, u64 m, R &ux,
+                                               R &uy, R &uz, ChildPool<R> &cb, int s, u64 i, uint32_t N,
+                                               uint32_t step) {
+    constexpr uint32_t kSeg = ChildPool<R>::kSeg;
+    const uint32_t c = (uint32_t)__popcll(m);
+    const int leader = __ffsll((long long)m) - 1;
+    uint32_t t = 0;
+    if (__lane_id() == leader) t = atomicAdd(&cb.tail, c);
+    t = __shfl(t, leader);
+    const uint32_t mine = t + (uint32_t)__popcll(m & lanemask_lt());
+    const R umag = sqrt_(em.u2);
+    em.inv = umag > R(0) ? rcp(umag) : R(0);
+    // the entries lie in one filling or in two
+    for (uint32_t f = t / kSeg; f <= (t + c - 1) / kSeg; ++f) {
+        const uint32_t half = f & 1u;
+        while (__hip_atomic_load(&cb.freed[half], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) != f >> 1)
+            __builtin_amdgcn_s_sleep(4);
+        if (em.acc && mine / kSeg == f) {
+            const uint32_t e = mine % (2 * kSeg);
+            put_child(cb, e, org, em, ux, uy, uz);
+            if (dst_ptr<true>(cb.dst.birth)) {   // in-step cascades
+                const double t0 = a.gen ? a.sp[s].birth[i] : 0.0;
+                const double st = (a.dt - t0) / (double)N;
+                cb.tb[e] = t0 + (double)(em.k + 1) * st;
+            }
+        }
+        const uint32_t lo = t > f * kSeg ? t : f * kSeg, hi = t + c < (f + 1) * kSeg ? t + c : (f + 1) * kSeg;
+        uint32_t done = 0;
+        if (__lane_id() == leader)
+            done = hi - lo + __hip_atomic_fetch_add(&cb.written[half], hi - lo, __ATOMIC_ACQ_REL,
+                                                    __HIP_MEMORY_SCOPE_WORKGROUP);
+        done = __shfl(done, leader);
+        if (done == kSeg) flush_half(cb, half, a.seed, step);
+    }
+    if (em.acc) recoil(em, ux, uy, uz);
+}
+
+__device__ __forceinline__ void stage_emission(const StepArgs &a, const Origin<float> &org, Emission<float> &em, u64 m,
+                                               float &ux, float &uy, float &uz, ChildBuf &cb, uint32_t step) {
     const uint32_t c = (uint32_t)__popcll(m);
     __syncwarp();
-    if (cb.count + c > ChildBuf<R, TB>::kCap) flush_children(cb, a.sp[2], a.seed, step);
+    if (cb.count + c > ChildBuf::kCap) flush_children(cb, a.sp[2], a.seed, step);
     const uint32_t n0 = cb.count;
-    if (acc) {
-        const uint32_t e = n0 + (uint32_t)__popcll(m & lanemask_lt());
-        const R umag = sqrt_(u2);
-        const R inv = umag > R(0) ? rcp(umag) : R(0);
-        const R eph = x3 * g * inv;
-        cb.x[e] = org.x + (double)dx;
-        cb.y[e] = org.y + (double)dy;
-        cb.z[e] = org.z + (double)dz;
-        cb.px[e] = ux * eph;
-        cb.py[e] = uy * eph;
-        cb.pz[e] = uz * eph;
-        cb.w[e] = org.w;
-        cb.ctr[e] = ctr;
-        cb.parent[e] = pid;
-        if constexpr (TB) cb.tb[e] = t0 + (double)(k + 1) * st;
-        // gamma' = (1 - delta) gamma, same direction
-        const R g1 = omx3 * g;
-        const R u1 = sqrt_(fmax(g1 * g1 - R(1), R(0)));
-        const R sc = u1 * inv;
-        ux *= sc;
-        uy *= sc;
-        uz *= sc;
-        nev++;
+    if (em.acc) {
+        const float umag = sqrt_(em.u2);
+        em.inv = umag > 0.0f ? rcp(umag) : 0.0f;
+        put_child(cb, n0 + (uint32_t)__popcll(m & lanemask_lt()), org, em, ux, uy, uz);
+        recoil(em, ux, uy, uz);
     }
     __syncwarp();
     cb.count = n0 + c;
     __syncwarp();
 }
 
-// One sub-step of Algorithm 1 after the push constants are set: Boris push and
-// move, chi after the push, the candidate (x, y) of sub-step k and the acceptance
-// probability of eq. (1), y < 3 x^2 P(x^3) = (c b / x) ((1 - x^3) F(z) + x^6 G(z)),
-// z = x^3 / (b (1 - x^3)).  Shared by the sub-step loop and the pre-pass (which
-// finishes particles of one quiet sub-step), so both round identically.
-template <class R, int FK>
-struct SubStep {
-    R u2, g, x3, omx3, pm, y;
+// Push and move of one sub-step of Algorithm 1 and the quantum parameter after the
+// push.  Shared by the sub-step loop and the pre-pass (which finishes particles of one
+// quiet sub-step), so both round identically.
+template <class R>
+struct PushState {
+    R u2, ig, g, chi;  // |u|^2, 1 / gamma, gamma, chi
 };
 
 template <class R, int FK>
-__device__ __forceinline__ SubStep<R, FK> substep(const Lepton<R> &p, R hex, R hey, R hez, R hq, R e2, R str, R kcb,
-                                                  uint32_t k, uint32_t idlo, uint32_t idhi, uint32_t step,
-                                                  uint32_t klo, uint32_t khi, Draw<R> &draw, const SynTable<R> &tab,
-                                                  R &ux, R &uy, R &uz, R &dx, R &dy, R &dz, const Rot<R> &rs,
-                                                  uint32_t &guard) {
-    SubStep<R, FK> o;
-    // push: Boris rotation and move (pure magnetic field: with the held rotation;
-    // o.u2 is then not set, an emission takes |u|^2 itself)
-    R ig, vs;
+__device__ __forceinline__ void push_substep(const Lepton<R> &p, R hex, R hey, R hez, R hq, R e2, R str, R &ux, R &uy,
+                                             R &uz, R &dx, R &dy, R &dz, const Rot<R> &rs, PushState<R> &o,
+                                             uint32_t &guard) {
+    // push: Boris rotation and move (pure magnetic field: with the held rotation, rs;
+    // gamma and chi are then rs's and o is not set)
+    R vs;
     if constexpr (FK == 2) {
         rotate(ux, uy, uz, rs);
-        ig = rs.ig;
-        o.g = rs.g;
-        o.u2 = R(0);
         vs = rs.vs;
     } else {
         boris<R, FK>(ux, uy, uz, hex, hey, hez, hq, p.bx, p.by, p.bz);
-        ig = inv_gamma(ux, uy, uz, o.u2);
-        o.g = (R(1) + o.u2) * ig;
-        vs = str * ig;
+        o.ig = inv_gamma(ux, uy, uz, o.u2);
+        o.g = (R(1) + o.u2) * o.ig;
+        vs = str * o.ig;
     }
     dx += ux * vs;
     dy += uy * vs;
     dz += uz * vs;
     // quantum parameter after the push (pure magnetic field: held, the rotation keeps it)
-    R chi;
-    if constexpr (FK == 2)
-        chi = rs.chi;
-    else
-        chi = chi_sub<FK>(ux, uy, uz, o.g, p.ex, p.ey, p.ez, p.bx, p.by, p.bz, e2, guard);
-    // candidate x and test value y
-    R x;
-    draw.get(k, idlo, idhi, step, klo, khi, x, o.y);
+    if constexpr (FK != 2)
+        o.chi = chi_sub<FK>(ux, uy, uz, o.g, p.ex, p.ey, p.ez, p.bx, p.by, p.bz, e2, guard);
+}
+
+// Acceptance probability of eq. (1) for the candidate x: 3 x^2 P(x^3) =
+// (c b / x) ((1 - x^3) F(z) + x^6 G(z)), z = x^3 / (b (1 - x^3)).
+template <class R>
+__device__ __forceinline__ R accept_prob(R kcb, R chi, R ig, R x, const SynTable<R> &tab, R &x3, R &omx3) {
     const R x2 = x * x;
-    o.x3 = x2 * x;
-    o.omx3 = (R(1) - x) * (R(1) + x + x2);
+    x3 = x2 * x;
+    omx3 = (R(1) - x) * (R(1) + x + x2);
     const R b = R(1.5) * chi;
-    const R z = o.x3 * rcp(b * o.omx3);
+    const R z = x3 * rcp(b * omx3);
     R F, G;
     syn_eval(z, tab, F, G);
-    o.pm = kcb * chi * ig * rcp(x) * (o.omx3 * F + o.x3 * o.x3 * G);
-    return o;
+    return kcb * chi * ig * rcp(x) * (omx3 * F + x3 * x3 * G);
+}
+
+// A kernel argument whose derived constants are formed where it is used, not kept in
+// vector registers across a particle loop.
+__device__ __forceinline__ double held_scalar(double v) {
+    asm volatile("" : "+s"(v));
+    return v;
 }
 
 // Push constants of a lepton (s = 0: q = -1, s = 1: q = +1) over sub-steps of st.
@@ -524,44 +683,112 @@ __device__ __forceinline__ Rot<R> rot_chi(const Lepton<R> &p, const PushConst<R>
 // Algorithm 1's sub-step loop for one electron (s = 0, q = -1) or positron (s = 1,
 // q = +1) with N >= 1 sub-steps.  s is uniform across the wave.  FK: field kind
 // (0 general, 1 pure E, 2 pure B), see boris().
+//
+// The loop is bound by VALU issue.  In a hot spot one sub-step in ninety of a lane emits,
+// so a wave that evaluated F and G at every sub-step, and ran the emission whenever
+// a lane has one, spent most of its instructions on them, the emission with one or two
+// active lanes.  Instead a table bounds the acceptance probability (qed_accept.hpp), and
+// a lane whose y falls below it waits (it does not advance) until a quarter of the
+// lanes still at work, or a.resolve_batch of them, wait too, or none can advance; then
+// they are evaluated and emit together.  A lane's own operations and draws do not depend
+// on when that happens, so every schedule gives the same result.  The float path draws
+// two sub-steps from one Philox block, so a pass of the loop runs both; a lane that
+// waits at the first of the two makes up the second after it is resolved, and all lanes
+// draw together again.  The 16.8M-electron hot spot's heavy queue: 1,890 us with every
+// candidate evaluated, 1,400 with the bound and the waiting lanes.
 template <class R, int FK>
 __device__ __forceinline__ void lepton_loop(const StepArgs &a, int s, u64 i, uint32_t N, Lepton<R> p,
-                                            const SynTable<R> &tab, ChildBuf<R> &cb, Tally<R> &tl, double t0) {
+                                            const SynTable<R> &tab, const AcceptTable &at, OriginHold<R> &oh,
+                                            ChildPool<R> &cb, Tally<R> &tl, double t0) {
+    constexpr bool kPairs = sizeof(R) == 4;   // two sub-steps per Philox block
     const SpeciesDev &sp = a.sp[s];
-    const uint64_t pid = sp.id[i];
-    const Origin<R> org = origin_of<R>(sp, i);
+    Origin<R> held{};
+    const Origin<R> start = origin_of<R>(sp, i);
+    oh.put(start, held);
+    const uint64_t pid = start.id;
     const double st = (a.dt - t0) / (double)N;
     const PushConst<R> c = push_const(p, s, st);
     const uint32_t idlo = (uint32_t)pid, idhi = (uint32_t)(pid >> 32);
     const uint32_t klo = (uint32_t)a.seed, khi = (uint32_t)(a.seed >> 32);
     const uint32_t step = step_of(a);
+    const int batch = (int)a.resolve_batch;
+    const R kyb = c.kcb * Draw<R>::kYScale;
     R ux = p.ux, uy = p.uy, uz = p.uz;
     R dx = 0, dy = 0, dz = 0;
     uint32_t nev = 0;
     uint32_t last = 0;  // sub-steps done at this particle's previous event
     Rot<R> rs{};
-    if constexpr (FK == 2) rs = rot_chi(p, c, ux, uy, uz);
+    AcceptBound<R> ab{};
+    if constexpr (FK == 2) {
+        rs = rot_chi(p, c, ux, uy, uz);
+        ab = accept_bound(kyb, rs.chi, rs.ig, at);
+    }
+    PushState<R> o{};   // of the lane's latest sub-step: kept while it waits (pure magnetic field: rs has it)
+    uint32_t k = 0;     // next sub-step of this lane
+    uint32_t lim = N;   // N, or 0 while the candidate of sub-step k - 1 waits for its evaluation
     Draw<R> draw;
-    for (uint32_t k = 0; k < N; ++k) {
-        const SubStep<R, FK> o = substep<R, FK>(p, c.hex, c.hey, c.hez, c.hq, c.e2, c.str, c.kcb, k, idlo, idhi, step,
-                                                klo, khi, draw, tab, ux, uy, uz, dx, dy, dz, rs, tl.guard);
-        tl.max_p = fmax(tl.max_p, o.pm);
-        tl.clips += o.pm > R(1);
-        const bool acc = o.y < o.pm;
-        // emission: stage the photon in the wave's LDS buffer, recoil on the parent
+    auto advance = [&](int half) {
+        push_substep<R, FK>(p, c.hex, c.hey, c.hez, c.hq, c.e2, c.str, ux, uy, uz, dx, dy, dz, rs, o, tl.guard);
+        if constexpr (FK != 2) ab = accept_bound(kyb, o.chi, o.ig, at);
+        ++k;
+        lim = accept_may(draw.test(half), draw.xword(half), ab, at) ? 0u : N;
+    };
+    for (;;) {
+        u64 mp;   // lanes that wait
+        for (;;) {
+            if (k < lim) {
+                draw.block(k, idlo, idhi, step, klo, khi);
+                advance(0);
+                if constexpr (kPairs) {
+                    if (k < lim) advance(1);
+                }
+            }
+            mp = __ballot(lim == 0u);
+            const u64 mr = __ballot(k < lim);
+            const int np = __popcll(mp);
+            if (mr == 0 || (np != 0 && (np >= batch || 4 * np >= __popcll(mp | mr)))) break;
+        }
+        if (mp == 0) break;
+        const bool pend = lim == 0u;
+        bool acc = false;
+        R x3 = R(0), omx3 = R(1);
+        if constexpr (FK == 2) {
+            o.ig = rs.ig;
+            o.g = rs.g;
+            o.chi = rs.chi;
+        }
+        if (pend) {
+            R x, y;
+            draw.pair(k - 1u, x, y);
+            const R pm = accept_prob(c.kcb, o.chi, o.ig, x, tab, x3, omx3);
+            tl.max_p = fmax(tl.max_p, pm);
+            tl.clips += pm > R(1);
+            acc = y < pm;
+            lim = N;
+        }
+        // emission: stage the photon, recoil on the parent
         const u64 m = __ballot(acc);
         if (m) {
             const R u2 = FK == 2 ? ux * ux + uy * uy + uz * uz : o.u2;
-            stage_emission<R>(a, org, pid, k, k, acc, m, o.x3, o.omx3, o.g, u2, dx, dy, dz, ux, uy, uz, cb, nev,
-                              t0, st, step);
-            if constexpr (FK == 2)
-                if (acc) rs = rot_chi(p, c, ux, uy, uz);   // after the recoil
-            if (acc && a.gap_hist) {
-                count_gap(a, 0, k + 1 - last);
-                last = k + 1;
+            Emission<R> em{acc, k - 1u, k - 1u, x3, omx3, o.g, u2, R(0), dx, dy, dz};
+            stage_emission(a, oh.get(held), em, m, ux, uy, uz, cb, s, i, N, step);
+            if (acc) {
+                nev++;
+                if constexpr (FK == 2) {   // after the recoil
+                    rs = rot_chi(p, c, ux, uy, uz);
+                    ab = accept_bound(kyb, rs.chi, rs.ig, at);
+                }
+                if (a.gap_hist) {
+                    count_gap(a, 0, k - last);
+                    last = k;
+                }
             }
         }
+        if constexpr (kPairs) {
+            if (pend && (k & 1u) != 0u && k < N) advance(1);
+        }
     }
+    const Origin<R> org = oh.get(held);
     ((R *)sp.ux)[i] = ux;
     ((R *)sp.uy)[i] = uy;
     ((R *)sp.uz)[i] = uz;
@@ -575,15 +802,16 @@ __device__ __forceinline__ void lepton_loop(const StepArgs &a, int s, u64 i, uin
 
 template <class R>
 __device__ __forceinline__ void lepton_run(const StepArgs &a, int s, u64 i, uint32_t N, Lepton<R> p,
-                                           const SynTable<R> &tab, ChildBuf<R> &cb, Tally<R> &tl, double t0) {
+                                           const SynTable<R> &tab, const AcceptTable &at, OriginHold<R> &oh,
+                                           ChildPool<R> &cb, Tally<R> &tl, double t0) {
     const bool noB = p.bx == R(0) && p.by == R(0) && p.bz == R(0);
     const bool noE = p.ex == R(0) && p.ey == R(0) && p.ez == R(0);
     if (noB)
-        lepton_loop<R, 1>(a, s, i, N, p, tab, cb, tl, t0);
+        lepton_loop<R, 1>(a, s, i, N, p, tab, at, oh, cb, tl, t0);
     else if (noE)
-        lepton_loop<R, 2>(a, s, i, N, p, tab, cb, tl, t0);
+        lepton_loop<R, 2>(a, s, i, N, p, tab, at, oh, cb, tl, t0);
     else
-        lepton_loop<R, 0>(a, s, i, N, p, tab, cb, tl, t0);
+        lepton_loop<R, 0>(a, s, i, N, p, tab, at, oh, cb, tl, t0);
 }
 
 // ---------------------------------------------------------------------------
@@ -687,12 +915,12 @@ __device__ __forceinline__ void substep_surr(const Lepton<float> &p, const PushC
 template <int FK, bool DUAL>
 __device__ __forceinline__ void lepton_loop_surr(const StepArgs &a, int s, u64 i, uint32_t N,
                                                  const Lepton<float> &p, const SynTable<float> &tab, SurrLds &S,
-                                                 ChildBuf<float, false> &cb, Tally<float> &tl) {
+                                                 ChildBuf &cb, Tally<float> &tl) {
     using R = float;
     const SpeciesDev &sp = a.sp[s];
     const bool has = N > 0;
-    const uint64_t pid = has ? sp.id[i] : 0ull;
-    const Origin<R> org = has ? origin_of<R>(sp, i) : Origin<R>{0.0, 0.0, 0.0, R(0)};
+    const Origin<R> org = has ? origin_of<R>(sp, i) : Origin<R>{0.0, 0.0, 0.0, R(0), 0ull};
+    const uint64_t pid = org.id;
     const double st = has ? a.dt / (double)N : 0.0;
     const PushConst<R> c = push_const(p, s, st);
     const R e2 = c.e2;
@@ -802,8 +1030,9 @@ __device__ __forceinline__ void lepton_loop_surr(const StepArgs &a, int s, u64 i
             x3 = x2 * x;
             omx3 = (R(1) - x) * (R(1) + x + x2);
         }
-        stage_emission<R>(a, org, pid, nev, pk, pend, mp, x3, omx3, cg, cu2, dx, dy, dz, ux, uy, uz, cb, nev,
-                          0.0, st, step);
+        Emission<R> em{pend, nev, pk, x3, omx3, cg, cu2, R(0), dx, dy, dz};
+        stage_emission(a, org, em, mp, ux, uy, uz, cb, step);
+        nev += pend;
         // The part of the sub-step after the crossing (the overshoot, at the rate before
         // the emission) counts against the new optical depth at the rate after the
         // recoil.  If that crosses it again, the lane waits for another emission
@@ -847,8 +1076,8 @@ template <class R>
 struct LeptonRunner<R, false> {
     template <bool DUAL = false, class L>
     __device__ static void run(const StepArgs &a, int s, u64 i, uint32_t N, const Lepton<R> &p, L &lds,
-                               ChildBuf<R> &cb, Tally<R> &t, double t0 = 0.0) {
-        if (N) lepton_run<R>(a, s, i, N, p, lds.tab, cb, t, t0);
+                               ChildPool<R> &cb, Tally<R> &t, double t0 = 0.0) {
+        if (N) lepton_run<R>(a, s, i, N, p, lds.tab, lds.acc, lds.org, cb, t, t0);
     }
 };
 
@@ -856,7 +1085,7 @@ template <>
 struct LeptonRunner<float, true> {
     template <bool DUAL = false, class L>
     __device__ static void run(const StepArgs &a, int s, u64 i, uint32_t n, const Lepton<float> &p, L &lds,
-                               ChildBuf<float, false> &cb, Tally<float> &t, double = 0.0) {
+                               ChildBuf &cb, Tally<float> &t, double = 0.0) {
         if (__ballot(n != 0) == 0) return;
         // one field kind for the whole wave (the general form is valid for all)
         const bool noB = p.bx == 0.0f && p.by == 0.0f && p.bz == 0.0f;
@@ -1005,11 +1234,24 @@ __device__ __forceinline__ int nbin(uint32_t N, uint32_t light_max, uint32_t per
 // ---------------------------------------------------------------------------
 // Kernels
 // ---------------------------------------------------------------------------
-// End-of-kernel flush of all wave buffers of the block with one atomic: every
-// thread of the block must call it.
-template <class R, bool TB>
-__device__ __forceinline__ void flush_children_block(ChildBuf<R, TB> *cbs, const SpeciesDev &dst, uint64_t seed,
-                                                     uint32_t step) {
+// End-of-kernel flush of what the block's pool, or its waves' buffers, still hold, with
+// one atomic: every thread of the block must call it.
+template <class R>
+__device__ __forceinline__ void flush_children_block(ChildPool<R> &cb, const SpeciesDev &, uint64_t seed, uint32_t step) {
+    constexpr uint32_t kSeg = ChildPool<R>::kSeg;
+    __shared__ u64 base_sh;
+    __syncthreads();
+    // complete halves have been written out: the last filling's first entries are left
+    const uint32_t left = cb.tail % kSeg, first = cb.tail % (2 * kSeg) - left;
+    if (left == 0) return;   // the same in every thread
+    if (threadIdx.x == 0) base_sh = atomicAdd(cb.dst.n, (u64)left);
+    __syncthreads();
+    for (uint32_t e = threadIdx.x; e < left; e += kBlock)
+        store_child<true>(cb, first + e, cb.dst, base_sh + e, seed, step);
+}
+
+__device__ __forceinline__ void flush_children_block(ChildBuf (&cbs)[kBlock / 64], const SpeciesDev &dst,
+                                                     uint64_t seed, uint32_t step) {
     __shared__ u64 base_sh;
     __shared__ uint32_t pre[kBlock / 64 + 1];
     __syncthreads();
@@ -1027,46 +1269,42 @@ __device__ __forceinline__ void flush_children_block(ChildBuf<R, TB> *cbs, const
     for (uint32_t e = threadIdx.x; e < total; e += kBlock) {
         int w = 0;
         while (w + 1 < kBlock / 64 && pre[w + 1] <= e) ++w;
-        const ChildBuf<R, TB> &cb = cbs[w];
-        const uint32_t k = e - pre[w];
-        const u64 slot = base_sh + e;
-        if (slot < dst.cap) {
-            dst.x[slot] = cb.x[k];
-            dst.y[slot] = cb.y[k];
-            dst.z[slot] = cb.z[k];
-            ((R *)dst.ux)[slot] = cb.px[k];
-            ((R *)dst.uy)[slot] = cb.py[k];
-            ((R *)dst.uz)[slot] = cb.pz[k];
-            ((R *)dst.w)[slot] = cb.w[k];
-            dst.id[slot] = child_id(seed, cb.parent[k], step, cb.ctr[k], 0);
-            if (dst.parent) dst.parent[slot] = cb.parent[k];
-            if constexpr (TB)
-                if (dst.birth) dst.birth[slot] = cb.tb[k];
-            if (dst.tau) dst.tau[slot] = -1.0;
-        }
+        store_child<false>(cbs[w], e - pre[w], dst, base_sh + e, seed, step);
     }
 }
 
-// LDS of the lepton kernels: the coefficient table and one child buffer per wave,
-// plus the rate table and the network for the surrogate sampler.
+// LDS of the lepton kernels: the coefficient tables and the staged children, plus the
+// rate table and the network for the surrogate sampler.
 template <class R, bool SURR>
 struct LeptonLds {
     SynTable<R> tab;
-    ChildBuf<R> cb[kBlock / 64];
+    AcceptTable acc;
+    OriginHold<R> org;
+    ChildPool<R> cb;
 };
 
 template <>
 struct LeptonLds<float, true> {
     SynTable<float> tab;
-    ChildBuf<float, false> cb[kBlock / 64];
+    ChildBuf cb[kBlock / 64];
     SurrLds surr;
 };
 
-template <class R, bool SURR>
-__device__ __forceinline__ auto &lepton_lds_init(const StepArgs &a, LeptonLds<R, SURR> &L) {
+template <class R>
+__device__ __forceinline__ ChildPool<R> &lepton_lds_init(const StepArgs &a, LeptonLds<R, false> &L) {
+    if (threadIdx.x == 0) {
+        L.cb.tail = L.cb.written[0] = L.cb.written[1] = L.cb.freed[0] = L.cb.freed[1] = 0;
+        L.cb.dst = a.sp[2];
+    }
+    accept_stage(L.acc);
+    syn_stage(L.tab);  // ends with a block barrier
+    return L.cb;
+}
+
+__device__ __forceinline__ ChildBuf &lepton_lds_init(const StepArgs &a, LeptonLds<float, true> &L) {
     auto &cb = L.cb[threadIdx.x / 64];
     if (__lane_id() == 0) cb.count = 0;
-    if constexpr (SURR) surr_stage(a, L.surr);
+    surr_stage(a, L.surr);
     syn_stage(L.tab);  // ends with a block barrier
     return cb;
 }
@@ -1083,41 +1321,17 @@ __device__ __forceinline__ uint32_t lepton_fetch(const StepArgs &a, int s, u64 i
     return lepton_nsub(a, s, i, p, t, dt);
 }
 
-// Naive scheduler: one lane per particle in buffer order; the loop runs with
-// whole waves (lanes past the end carry no particle).  The pass covers the slots
-// lo..hi of the device state; in a cascade pass (gen >= 1) each particle runs
-// over the rest of the step from its birth time.
-template <class R, bool SURR>
-__global__ __launch_bounds__(kBlock) void k_lepton(StepArgs a) {
-    __shared__ LeptonLds<R, SURR> L;
-    auto &cb = lepton_lds_init<R, SURR>(a, L);
-    const int s = blockIdx.y;
-    const u64 lo = a.st->lo[s], hi = a.st->hi[s];
-    Tally<R> t;
-    for (u64 i0 = lo + (u64)blockIdx.x * kBlock + (threadIdx.x & ~63u); i0 < hi; i0 += (u64)gridDim.x * kBlock) {
-        const u64 i = i0 + __lane_id();
-        const bool has = i < hi;
-        const double t0 = a.gen && has ? a.sp[s].birth[i] : 0.0;
-        Lepton<R> p;
-        const uint32_t N = lepton_fetch(a, s, i, has, p, t, a.dt - t0);
-        if (has && N == 0 && a.sp[s].events) a.sp[s].events[i] = 0;
-        LeptonRunner<R, SURR>::run(a, s, i, N, p, L, cb, t, t0);
-    }
-    flush_children_block(L.cb, a.sp[2], a.seed, step_of(a));
-    flush_tally(t, a.st, s);
-}
-
 // A particle whose step has a single sub-step (N = 1, main pass) runs it here.  If
 // it ends without an event the particle is finished: it is stored as the sub-step
 // loop would store it (the same shared sub-step code, so bit for bit the same) and
 // true is returned.  If it emits (or its optical depth runs out), nothing is
-// written and false is returned: the light pass then runs the particle in full.
+// written and false is returned: the caller's loop then runs the particle in full.
 template <class R, int FK>
 __device__ __forceinline__ bool finish_single_fk(const StepArgs &a, int s, u64 i, const Lepton<R> &p,
-                                                 const SynTable<R> &tab, Tally<R> &tl) {
+                                                 const SynTable<R> &tab, const AcceptTable &at, Tally<R> &tl) {
     const SpeciesDev &sp = a.sp[s];
     const uint64_t pid = sp.id[i];
-    const double st = a.dt;
+    const double st = held_scalar(a.dt);
     const PushConst<R> c = push_const(p, s, st);
     R ux = p.ux, uy = p.uy, uz = p.uz;
     R dx = 0, dy = 0, dz = 0;
@@ -1125,12 +1339,22 @@ __device__ __forceinline__ bool finish_single_fk(const StepArgs &a, int s, u64 i
     if constexpr (FK == 2) rs = rot_chi(p, c, ux, uy, uz);
     uint32_t guard = 0;
     Draw<R> draw;
-    const SubStep<R, FK> o = substep<R, FK>(p, c.hex, c.hey, c.hez, c.hq, c.e2, c.str, c.kcb, 0u, (uint32_t)pid,
-                                            (uint32_t)(pid >> 32), step_of(a), (uint32_t)a.seed,
-                                            (uint32_t)(a.seed >> 32), draw, tab, ux, uy, uz, dx, dy, dz, rs, guard);
-    if (o.y < o.pm) return false;
-    tl.max_p = fmax(tl.max_p, o.pm);
-    tl.clips += o.pm > R(1);
+    PushState<R> o;
+    push_substep<R, FK>(p, c.hex, c.hey, c.hez, c.hq, c.e2, c.str, ux, uy, uz, dx, dy, dz, rs, o, guard);
+    if constexpr (FK == 2) {
+        o.ig = rs.ig;
+        o.chi = rs.chi;
+    }
+    draw.block(0u, (uint32_t)pid, (uint32_t)(pid >> 32), step_of(a), (uint32_t)a.seed, (uint32_t)(a.seed >> 32));
+    const AcceptBound<R> ab = accept_bound(c.kcb * Draw<R>::kYScale, o.chi, o.ig, at);
+    if (accept_may(draw.test(0), draw.xword(0), ab, at)) {
+        R x, y, x3, omx3;
+        draw.pair(0u, x, y);
+        const R pm = accept_prob(c.kcb, o.chi, o.ig, x, tab, x3, omx3);
+        if (y < pm) return false;
+        tl.max_p = fmax(tl.max_p, pm);
+        tl.clips += pm > R(1);
+    }
     tl.guard += guard;
     ((R *)sp.ux)[i] = ux;
     ((R *)sp.uy)[i] = uy;
@@ -1148,7 +1372,7 @@ __device__ __forceinline__ bool finish_single_surr_fk(const StepArgs &a, int s, 
                                                       const RateTable &rate, Tally<float> &tl) {
     const SpeciesDev &sp = a.sp[s];
     const uint64_t pid = sp.id[i];
-    const double st = a.dt;
+    const double st = held_scalar(a.dt);
     const PushConst<float> c = push_const(p, s, st);
     const float wk = (float)(kAlpha * st);
     double tau = sp.tau[i];
@@ -1186,6 +1410,7 @@ template <class R, bool SURR>
 struct PrepassLds {
     uint32_t h[kBins];
     SynTable<R> tab;
+    AcceptTable acc;
 };
 
 template <>
@@ -1194,44 +1419,132 @@ struct PrepassLds<float, true> {
     RateTable rate;
 };
 
-template <class R, bool SURR>
-__device__ __forceinline__ bool finish_single(const StepArgs &a, int s, u64 i, const Lepton<R> &p,
-                                              const PrepassLds<R, SURR> &L, Tally<R> &tl) {
+// L: LDS with the tables (tab and acc, or the rate table on the optical-depth path).
+__device__ __forceinline__ const RateTable &rate_of(const PrepassLds<float, true> &L) { return L.rate; }
+__device__ __forceinline__ const RateTable &rate_of(const LeptonLds<float, true> &L) { return L.surr.rate; }
+
+template <class R, bool SURR, class L>
+__device__ __forceinline__ bool finish_single(const StepArgs &a, int s, u64 i, const Lepton<R> &p, const L &lds,
+                                              Tally<R> &tl) {
     // the field kind of the push and chi as the loops choose it (every kind gives the
     // general form's result for its fields)
     const bool noB = p.bx == R(0) && p.by == R(0) && p.bz == R(0);
     const bool noE = p.ex == R(0) && p.ey == R(0) && p.ez == R(0);
     if constexpr (SURR) {
-        if (noB) return finish_single_surr_fk<1>(a, s, i, p, L.rate, tl);
-        if (noE) return finish_single_surr_fk<2>(a, s, i, p, L.rate, tl);
-        return finish_single_surr_fk<0>(a, s, i, p, L.rate, tl);
+        if (noB) return finish_single_surr_fk<1>(a, s, i, p, rate_of(lds), tl);
+        if (noE) return finish_single_surr_fk<2>(a, s, i, p, rate_of(lds), tl);
+        return finish_single_surr_fk<0>(a, s, i, p, rate_of(lds), tl);
     } else {
-        if (noB) return finish_single_fk<R, 1>(a, s, i, p, L.tab, tl);
-        if (noE) return finish_single_fk<R, 2>(a, s, i, p, L.tab, tl);
-        return finish_single_fk<R, 0>(a, s, i, p, L.tab, tl);
+        if (noB) return finish_single_fk<R, 1>(a, s, i, p, lds.tab, lds.acc, tl);
+        if (noE) return finish_single_fk<R, 2>(a, s, i, p, lds.tab, lds.acc, tl);
+        return finish_single_fk<R, 0>(a, s, i, p, lds.tab, lds.acc, tl);
     }
+}
+
+// Naive scheduler: every wave takes 64 particles in buffer order.  The pass covers the
+// slots lo..hi of the device state; in a cascade pass (gen >= 1) each particle runs over
+// the rest of the step from its birth time.
+//
+// On the optical-depth path the particles of a single sub-step without an event, nearly
+// all of a laser field's, end right there (finish_single); the others go to a queue of
+// the wave in LDS, which is run 64 particles at a time, so that their emissions and
+// network passes run with full waves instead of one or two lanes (1.05M electrons in the
+// laser field, 1.8% emitting: 73 to 60 us).  Where at least half of the 64 are left they
+// run at once, without reading their records again.  Algorithm 1's loop, whose
+// particles of two and more sub-steps are a third there, is better off without the
+// second read (54 against 61 us).
+constexpr uint32_t kLeptonQueue = 128;   // at most 63 + 31 queued
+
+template <class R, bool SURR>
+__global__ __launch_bounds__(kBlock, SURR ? 2 : sizeof(R) == 4 ? 4 : 3) void k_lepton(StepArgs a) {
+    __shared__ LeptonLds<R, SURR> L;
+    __shared__ uint32_t slot_sh[SURR ? kBlock / 64 : 1][kLeptonQueue], n_sh[SURR ? kBlock / 64 : 1][kLeptonQueue];
+    const int s = blockIdx.y;
+    const u64 lo = a.st->lo[s], hi = a.st->hi[s];
+    if (lo + (u64)blockIdx.x * kBlock >= hi) return;   // no particle for this block: nothing to stage
+    auto &cb = lepton_lds_init(a, L);
+    const uint32_t lane = __lane_id();
+    const uint32_t wv = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+    Tally<R> t;
+    const u64 G = first_lane((u64)gridDim.x * kBlock);
+    u64 i0 = first_lane(lo + (u64)blockIdx.x * kBlock + (threadIdx.x & ~63u));
+    if constexpr (SURR) {
+        uint32_t *qslot = slot_sh[wv], *qn = n_sh[wv];   // slot - lo, sub-steps
+        uint32_t queued = 0;   // wave-uniform
+        for (;; i0 += G) {
+            const bool more = i0 < hi;   // the last passes of the loop run what is still queued
+            u64 i = i0 + lane;
+            Lepton<R> p;
+            uint32_t N = 0;
+            u64 m = 0;
+            if (more) {
+                const bool has = i < hi;
+                N = lepton_fetch(a, s, i, has, p, t, a.dt);
+                if (has && N == 0 && a.sp[s].events) a.sp[s].events[i] = 0;
+                if (N == 1 && finish_single<R, SURR>(a, s, i, p, L, t)) N = 0;
+                m = __ballot(N != 0);
+            }
+            if (__popcll(m) < 32) {
+                if (N) {
+                    const uint32_t q = queued + (uint32_t)__popcll(m & lanemask_lt());
+                    qslot[q] = (uint32_t)(i - lo);
+                    qn[q] = N;
+                }
+                queued += (uint32_t)__popcll(m);
+                __syncwarp();
+                if (more && queued < 64) continue;
+                // the newest 64, or the rest at the end (at most 94 queued: two passes)
+                const uint32_t run = queued < 64 ? queued : 64;
+                if (run == 0) break;
+                queued -= run;
+                const bool has = lane < run;
+                i = lo + (has ? qslot[queued + lane] : 0u);
+                N = has ? qn[queued + lane] : 0u;
+                __syncwarp();
+                p = has ? load_lepton<R>(a, s, i) : Lepton<R>{0, 0, 0, 0, 0, 0, 0, 0, 0};
+            }
+            LeptonRunner<R, SURR>::run(a, s, i, N, p, L, cb, t);
+            if (!more && queued == 0) break;
+        }
+    } else {
+        for (; i0 < hi; i0 += G) {
+            const u64 i = i0 + lane;
+            const bool has = i < hi;
+            const double t0 = a.gen && has ? a.sp[s].birth[i] : 0.0;
+            Lepton<R> p;
+            const uint32_t N = lepton_fetch(a, s, i, has, p, t, a.dt - t0);
+            if (has && N == 0 && a.sp[s].events) a.sp[s].events[i] = 0;
+            LeptonRunner<R, SURR>::run(a, s, i, N, p, L, cb, t, t0);
+        }
+    }
+    flush_children_block(L.cb, a.sp[2], a.seed, step_of(a));
+    flush_tally(t, a.st, s);
 }
 
 // Pre-pass of the binned scheduler: every lepton's sub-step count N (the bound of
 // Sec. 3.1.1 in double) and the histogram of the bins.  With a.prepass_finish,
 // particles of a single quiet sub-step are finished here (N recorded as 0, like a
 // skipped particle), so the light pass does not read them again.  A streaming pass:
-// the float instances are held to 128 VGPRs so that 4 waves per SIMD hide its loads.
+// the float instances are held to the registers at which kPrepassBlocks blocks per
+// compute unit are resident and hide its loads.
 template <class R, bool SURR>
-__global__ __launch_bounds__(kBlock, sizeof(R) == 4 ? 4 : 3) void k_prepass(StepArgs a) {
+__global__ __launch_bounds__(kBlock, sizeof(R) == 4 ? kPrepassBlocks[SURR] : 4) void k_prepass(StepArgs a) {
     __shared__ PrepassLds<R, SURR> L;
     uint32_t *h = L.h;
     const int s = blockIdx.y;
+    const u64 n = a.st->n0[s];
+    if ((u64)blockIdx.x * kBlock >= n) return;
     for (int b = threadIdx.x; b < kBins; b += kBlock) h[b] = 0;
     if (a.prepass_finish) {
-        if constexpr (SURR)
+        if constexpr (SURR) {
             rate_stage(L.rate);  // ends with a barrier
-        else
+        } else {
+            accept_stage(L.acc);
             syn_stage(L.tab);    // ends with a barrier
+        }
     } else {
         __syncthreads();
     }
-    const u64 n = a.st->n0[s];
     Tally<R> t;
     for (u64 i = (u64)blockIdx.x * kBlock + threadIdx.x; i < n; i += (u64)gridDim.x * kBlock) {
         const Lepton<R> p = load_lepton<R>(a, s, i);
@@ -1292,6 +1605,7 @@ __global__ __launch_bounds__(kBlock) void k_scatter(StepArgs a) {
     const u64 n = a.st->n0[s];
     const u64 per = ((n + gridDim.x - 1) / gridDim.x + kBlock - 1) / kBlock * kBlock;
     const u64 lo = (u64)blockIdx.x * per;
+    if (lo >= n) return;
     const u64 hi = lo + per < n ? lo + per : n;
     for (int b = threadIdx.x; b < kBins; b += kBlock) cnt[b] = 0;
     __syncthreads();
@@ -1347,9 +1661,10 @@ __global__ __launch_bounds__(kBlock) void k_light(StepArgs a) {
     __shared__ LeptonLds<R, SURR> L;
     __shared__ uint32_t hist_sh[kBlock / 64][kTileKeys];
     __shared__ uint16_t order_sh[kBlock / 64][kTile];
-    auto &cb = lepton_lds_init<R, SURR>(a, L);
     const int s = blockIdx.y;
     const u64 n = a.st->n0[s];
+    if ((u64)blockIdx.x * (kBlock / 64) * a.light_tile >= n) return;
+    auto &cb = lepton_lds_init(a, L);
     const uint32_t lmax = a.light_max;
     const uint32_t lane = __lane_id();
     const int wv = threadIdx.x / 64;
@@ -1414,9 +1729,10 @@ __global__ __launch_bounds__(kBlock) void k_tiled(StepArgs a) {
     __shared__ uint32_t hist_sh[kBlock / 64][kTileKeys];
     __shared__ uint16_t order_sh[kBlock / 64][kTiledSlots];
     __shared__ uint32_t nsub_sh[kBlock / 64][kTiledSlots];
-    auto &cb = lepton_lds_init<R, SURR>(a, L);
     const int s = blockIdx.y;
     const u64 n = a.st->n0[s];
+    if ((u64)blockIdx.x * (kBlock / 64) * a.tiled_slots >= n) return;
+    auto &cb = lepton_lds_init(a, L);
     const uint32_t lane = __lane_id();
     const int wv = threadIdx.x / 64;
     uint32_t *hist = hist_sh[wv];
@@ -1476,17 +1792,18 @@ __global__ __launch_bounds__(kBlock) void k_tiled(StepArgs a) {
 // buffers) fits two blocks per compute unit, so it is compiled for two waves per
 // SIMD and may use the registers that allows.
 template <class R, bool SURR>
-__global__ __launch_bounds__(kBlock, SURR ? 2 : 3) void k_heavy(StepArgs a) {
+__global__ __launch_bounds__(kBlock, SURR ? 2 : sizeof(R) == 4 ? 4 : 3) void k_heavy(StepArgs a) {
     __shared__ LeptonLds<R, SURR> L;
-    auto &cb = lepton_lds_init<R, SURR>(a, L);
     const int s = blockIdx.y;
     const u64 H = a.st->heavy[s];
     const uint32_t chunk = a.chunk;
+    if ((u64)blockIdx.x * (kBlock / 64) * chunk >= H) return;   // nor does the queue, which starts after these, hold any
+    auto &cb = lepton_lds_init(a, L);
     Tally<R> t;
     // the first chunk of every wave is assigned statically; later ones are
     // claimed from the queue, which starts after all static chunks
     const u64 nwaves = (u64)gridDim.x * (kBlock / 64);
-    u64 base = ((u64)blockIdx.x * (kBlock / 64) + threadIdx.x / 64) * chunk;
+    u64 base = first_lane(((u64)blockIdx.x * (kBlock / 64) + threadIdx.x / 64) * chunk);
     for (;;) {
         if (base >= H) break;
         const u64 end = base + chunk < H ? base + chunk : H;
@@ -1501,7 +1818,7 @@ __global__ __launch_bounds__(kBlock, SURR ? 2 : 3) void k_heavy(StepArgs a) {
         }
         u64 nb = 0;
         if (__lane_id() == 0) nb = nwaves * chunk + atomicAdd(&a.st->queue[s], (u64)chunk);
-        base = __shfl(nb, 0);
+        base = first_lane(nb);
     }
     flush_children_block(L.cb, a.sp[2], a.seed, step_of(a));
     flush_tally(t, a.st, s, 1);
@@ -1544,9 +1861,10 @@ __global__ __launch_bounds__(kBlock) void k_photon(StepArgs a) {
     __shared__ R qk_sh[kBlock / 64][3][kPhotonQueue];
     __shared__ uint32_t qn_sh[kBlock / 64][kPhotonQueue];
     __shared__ PairTable pt;
+    const u64 lo = a.st->lo[2], n = a.st->hi[2];
+    if (lo + (u64)blockIdx.x * kBlock >= n) return;
     pair_stage(pt);
     syn_stage(tab);
-    const u64 lo = a.st->lo[2], n = a.st->hi[2];
     const SpeciesDev &sp = a.sp[2];
     const FieldDev &fl = a.fl[2];
     const bool uni = fl.stride == 0;
@@ -1734,11 +2052,12 @@ __global__ __launch_bounds__(kBlock) void k_photon_surr(StepArgs a) {
     __shared__ SynTable<float> tab;
     __shared__ PairTable pt;
     __shared__ PairNetLds<NET> net;
+    using R = float;
+    const u64 n = a.st->hi[2];
+    if ((u64)blockIdx.x * kBlock >= n) return;
     if constexpr (NET) mlp_stage(a.pair_model, net.M);
     pair_stage(pt);
     syn_stage(tab);
-    using R = float;
-    const u64 n = a.st->hi[2];
     const SpeciesDev &sp = a.sp[2];
     const SpeciesDev &el = a.sp[0];
     const SpeciesDev &po = a.sp[1];
