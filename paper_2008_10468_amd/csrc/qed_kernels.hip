@@ -1796,13 +1796,21 @@ __global__ __launch_bounds__(kBlock, SURR ? 2 : sizeof(R) == 4 ? 4 : 3) void k_h
     __shared__ LeptonLds<R, SURR> L;
     const int s = blockIdx.y;
     const u64 H = a.st->heavy[s];
-    const uint32_t chunk = a.chunk;
+    // A wave's chunk: the tuned one while the queue has one for every wave of the grid,
+    // else its share, so that a short queue is spread over all of them: whole waves of 64
+    // while there are that many, then down to 16 entries, one row group of the network
+    // (fewer lanes resolve fewer emissions at a time, and the longest chain of emissions of
+    // a lane sets the time).  300,000 electrons, 30,000 of them heavy, at a chunk of 256 on
+    // 2,048 waves: 549 us on 117 of them, 126 on 1,878.
+    const u64 nwaves = (u64)gridDim.x * (kBlock / 64);
+    const u64 fair = (H + nwaves - 1) / nwaves;
+    const uint32_t grain = fair > 32 ? 64u : 16u;
+    const uint32_t chunk = fair >= a.chunk ? a.chunk : (uint32_t)((fair + grain - 1) / grain * grain);
     if ((u64)blockIdx.x * (kBlock / 64) * chunk >= H) return;   // nor does the queue, which starts after these, hold any
     auto &cb = lepton_lds_init(a, L);
     Tally<R> t;
     // the first chunk of every wave is assigned statically; later ones are
     // claimed from the queue, which starts after all static chunks
-    const u64 nwaves = (u64)gridDim.x * (kBlock / 64);
     u64 base = first_lane(((u64)blockIdx.x * (kBlock / 64) + threadIdx.x / 64) * chunk);
     for (;;) {
         if (base >= H) break;
