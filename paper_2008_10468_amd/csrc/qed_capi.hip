@@ -49,10 +49,10 @@ struct qed_ctx {
     std::vector<void *> retired;  // replaced scratch: recorded graphs may still use it
     // tile-sorted deposition: per-slot ranks and records (dep_cap slots), tile counts (zero between calls) and offsets (dep_tiles tiles), the
     // parts' tiles and staged regions (dep_parts parts)
-    uint32_t *dep_pos, *dep_count, *dep_off, *dep_part_off, *dep_part_tile;
+    uint32_t *dep_pos, *dep_count, *dep_off, *dep_part_off, *dep_part_tile, *dep_rows;
     qed::DepRecord *dep_rec;
     double *dep_stage;
-    u64 dep_cap, dep_tiles, dep_parts;
+    u64 dep_cap, dep_tiles, dep_parts, dep_row_tiles;
 };
 
 struct qed_graph {
@@ -236,7 +236,9 @@ qed_status ensure_cell_slots(qed_ctx *c, int s, u64 cap) {
 // graph, or out of memory: the caller then adds per wave).
 bool ensure_deposit_scratch(qed_ctx *c, u64 cap, u64 tiles) {
     const u64 parts = qed::dep_max_parts(cap, tiles);
-    if (cap <= c->dep_cap && tiles <= c->dep_tiles && parts <= c->dep_parts) return true;
+    const u64 row_tiles = qed::dep_by_rows(cap, tiles) ? tiles : 0;
+    if (cap <= c->dep_cap && tiles <= c->dep_tiles && parts <= c->dep_parts && row_tiles <= c->dep_row_tiles)
+        return true;
     if (c->capturing) return false;
     if (hipStreamSynchronize(c->stream) != hipSuccess) return false;
     bool ok = true;
@@ -266,6 +268,12 @@ bool ensure_deposit_scratch(qed_ctx *c, u64 cap, u64 tiles) {
         ok = hipMalloc(&c->dep_part_tile, parts * sizeof(uint32_t)) == hipSuccess &&
              hipMalloc(&c->dep_stage, parts * qed::kDepStage * sizeof(double)) == hipSuccess;
         if (ok) c->dep_parts = parts;
+    }
+    if (ok && row_tiles > c->dep_row_tiles) {
+        retire(c, c->dep_rows);
+        c->dep_row_tiles = 0;
+        ok = hipMalloc(&c->dep_rows, qed::kDepRows * row_tiles * sizeof(uint32_t)) == hipSuccess;
+        if (ok) c->dep_row_tiles = row_tiles;
     }
     if (!ok) (void)hipGetLastError();   // an allocation failure is not kept as the stream's error
     return ok;
@@ -818,6 +826,7 @@ qed_status qed_deposit(qed_ctx *c, const qed_grid *grid, const qed_species *sp, 
         d.pos = c->dep_pos;
         d.rec = c->dep_rec;
         d.stage = c->dep_stage;
+        d.rows = qed::dep_by_rows(sp->capacity, ntiles) ? c->dep_rows : nullptr;
         if (qed::launch_deposit_sorted(g, d, dtype, grid_for(sp->capacity, c->num_cu * 8), c->stream) != hipSuccess)
             return QED_ERR_HIP;
         return QED_OK;
@@ -1281,6 +1290,7 @@ void qed_finalize(qed_ctx *c) {
     release(c->dep_part_off);
     release(c->dep_part_tile);
     release(c->dep_stage);
+    release(c->dep_rows);
     for (void *b : c->retired) (void)hipFree(b);
     delete c;
 }

@@ -287,7 +287,8 @@ __global__ __launch_bounds__(kGridBlock) void k_deposit(GridDev g, DepositArgs a
 //   k_dep_bin      tile of every particle; its rank among the tile's particles (each
 //                  block counts its particles per tile in LDS and reserves a range of
 //                  every tile it touches with one atomic add; beyond kBinLdsTiles
-//                  tiles every particle reserves its own place)
+//                  tiles every particle reserves its own place); for many particles
+//                  and tiles k_dep_rows and k_dep_cols count row by row instead
 //   k_dep_scan     exclusive sums over the tiles of their particles and of their
 //                  parts (a part: up to kPart particles of one tile), the tile of each
 //                  part; clears the counts for the next call
@@ -359,6 +360,78 @@ __global__ __launch_bounds__(kGridBlock) void k_dep_bin(GridDev g, DepSortArgs a
     }
 }
 
+// The tiles counted row by row, without atomic adds on global memory (dep_by_rows): the
+// particles are cut into kDepRows contiguous rows; block b counts row b in LDS (a
+// particle's rank is its order in its tile within the row) and writes its counts;
+// k_dep_cols turns each tile's column of counts into first places and its total.
+constexpr int kRowBlock = 1024;
+
+// Particles per row; rows that hold particles.
+__device__ __forceinline__ u64 row_len(u64 n) {
+    return ((n + kDepRows - 1) / kDepRows + kRowBlock - 1) / kRowBlock * kRowBlock;
+}
+__device__ __forceinline__ uint32_t rows_used(u64 n) {
+    const u64 per = row_len(n);
+    return per ? (uint32_t)((n + per - 1) / per) : 0u;
+}
+
+__global__ __launch_bounds__(kRowBlock) void k_dep_rows(GridDev g, DepSortArgs a) {
+    extern __shared__ uint32_t row_sh[];   // ntiles
+    const u64 n0 = *a.n;
+    const u64 n = n0 < a.cap ? n0 : a.cap;
+    const u64 per = row_len(n), lo = (u64)blockIdx.x * per, hi = lo + per < n ? lo + per : n;
+    if (lo >= n) return;   // whole block
+    for (uint32_t i = threadIdx.x; i < a.ntiles; i += kRowBlock) row_sh[i] = 0;
+    __syncthreads();
+    for (u64 p = lo + threadIdx.x; p < hi; p += kRowBlock) {
+        const double x = a.x[p], y = a.y[p], z = a.z[p];
+        uint32_t rank = kNoTile;
+        if (on_grid(g, x, y, z)) {
+            uint32_t nd[3], local;
+            double ph[3];
+            node_cell(g, x, y, z, nd, ph);
+            rank = atomicAdd(&row_sh[tile_of(a, nd, local)], 1u);
+        }
+        a.pos[p] = rank;
+    }
+    __syncthreads();
+    uint32_t *row = a.rows + (u64)blockIdx.x * a.ntiles;
+    for (uint32_t i = threadIdx.x; i < a.ntiles; i += kRowBlock) row[i] = row_sh[i];
+}
+
+// 64 tiles per block (lanes), a quarter of the rows per wave.
+__global__ __launch_bounds__(kGridBlock) void k_dep_cols(DepSortArgs a) {
+    constexpr uint32_t kWaves = kGridBlock / 64, kPer = kDepRows / kWaves;
+    __shared__ uint32_t part[kWaves][64];
+    const u64 n0 = *a.n;
+    const uint32_t used = rows_used(n0 < a.cap ? n0 : a.cap);
+    const uint32_t lane = __lane_id(), wv = threadIdx.x / 64, t = blockIdx.x * 64 + lane;
+    uint32_t v[kPer], sum = 0;
+#pragma unroll
+    for (uint32_t k = 0; k < kPer; ++k) {
+        const uint32_t r = wv * kPer + k;
+        v[k] = t < a.ntiles && r < used ? a.rows[(u64)r * a.ntiles + t] : 0u;
+    }
+#pragma unroll
+    for (uint32_t k = 0; k < kPer; ++k) sum += v[k];
+    part[wv][lane] = sum;
+    __syncthreads();
+    uint32_t at = 0, total = 0;
+#pragma unroll
+    for (uint32_t w = 0; w < kWaves; ++w) {
+        at += w < wv ? part[w][lane] : 0u;
+        total += part[w][lane];
+    }
+    if (t >= a.ntiles) return;
+#pragma unroll
+    for (uint32_t k = 0; k < kPer; ++k) {
+        const uint32_t r = wv * kPer + k;
+        if (r < used) a.rows[(u64)r * a.ntiles + t] = at;
+        at += v[k];
+    }
+    if (wv == 0) a.count[t] = total;
+}
+
 // Inclusive sum over a block of kScanBlock threads (16 waves); total: the block's sum.
 constexpr int kScanBlock = 1024;
 
@@ -418,6 +491,24 @@ __global__ __launch_bounds__(kScanBlock) void k_dep_scan(DepSortArgs a) {
     }
 }
 
+// The record of particle p (on the grid) at place `at` of tile order.
+template <class R>
+__device__ __forceinline__ void put_record(const DepSortArgs &a, u64 p, const double ph[3], uint32_t local, u64 at,
+                                           double scale) {
+    const double ux = (double)((const R *)a.ux)[p], uy = (double)((const R *)a.uy)[p],
+                 uz = (double)((const R *)a.uz)[p];
+    const double w = (double)((const R *)a.w)[p];
+    const double gi = 1.0 / sqrt(1.0 + ux * ux + uy * uy + uz * uz);
+    const bool ok = isfinite(w * gi * (ux + uy + uz));
+    // one 64-byte line per record, written as four 16-byte stores
+    DepRecord *r = a.rec + at;
+    double2 *v = reinterpret_cast<double2 *>(r);
+    v[0] = make_double2(ph[0], ph[1]);
+    v[1] = make_double2(ph[2], ok ? scale * w * ux * gi : 0.0);
+    v[2] = make_double2(ok ? scale * w * uy * gi : 0.0, ok ? scale * w * uz * gi : 0.0);
+    reinterpret_cast<uint4 *>(r)[3] = make_uint4(local, 0u, 0u, 0u);
+}
+
 template <class R>
 __global__ __launch_bounds__(kGridBlock) void k_dep_scatter(GridDev g, DepSortArgs a) {
     const u64 n0 = *a.n;
@@ -426,23 +517,34 @@ __global__ __launch_bounds__(kGridBlock) void k_dep_scatter(GridDev g, DepSortAr
     for (u64 p = (u64)blockIdx.x * kGridBlock + threadIdx.x; p < n; p += (u64)gridDim.x * kGridBlock) {
         const uint32_t rank = a.pos[p];
         if (rank == kNoTile) continue;
-        const double x = a.x[p], y = a.y[p], z = a.z[p];
-        const double ux = (double)((const R *)a.ux)[p], uy = (double)((const R *)a.uy)[p],
-                     uz = (double)((const R *)a.uz)[p];
-        const double w = (double)((const R *)a.w)[p];
-        const double gi = 1.0 / sqrt(1.0 + ux * ux + uy * uy + uz * uz);
-        const bool ok = isfinite(w * gi * (ux + uy + uz));
         uint32_t nd[3], local;
         double ph[3];
-        node_cell(g, x, y, z, nd, ph);
+        node_cell(g, a.x[p], a.y[p], a.z[p], nd, ph);
         const uint32_t t = tile_of(a, nd, local);
-        // one 64-byte line per record, written as four 16-byte stores
-        DepRecord *r = a.rec + ((u64)a.off[t] + rank);
-        double2 *v = reinterpret_cast<double2 *>(r);
-        v[0] = make_double2(ph[0], ph[1]);
-        v[1] = make_double2(ph[2], ok ? scale * w * ux * gi : 0.0);
-        v[2] = make_double2(ok ? scale * w * uy * gi : 0.0, ok ? scale * w * uz * gi : 0.0);
-        reinterpret_cast<uint4 *>(r)[3] = make_uint4(local, 0u, 0u, 0u);
+        put_record<R>(a, p, ph, local, (u64)a.off[t] + rank, scale);
+    }
+}
+
+// The same row by row: block b holds the first place of row b in every tile in LDS.
+template <class R>
+__global__ __launch_bounds__(kRowBlock) void k_dep_scatter_rows(GridDev g, DepSortArgs a) {
+    extern __shared__ uint32_t row_sh[];   // ntiles
+    const u64 n0 = *a.n;
+    const u64 n = n0 < a.cap ? n0 : a.cap;
+    const u64 per = row_len(n), lo = (u64)blockIdx.x * per, hi = lo + per < n ? lo + per : n;
+    if (lo >= n) return;   // whole block
+    const uint32_t *row = a.rows + (u64)blockIdx.x * a.ntiles;
+    for (uint32_t i = threadIdx.x; i < a.ntiles; i += kRowBlock) row_sh[i] = a.off[i] + row[i];
+    __syncthreads();
+    const double scale = a.charge * g.idx * g.idy * g.idz;
+    for (u64 p = lo + threadIdx.x; p < hi; p += kRowBlock) {
+        const uint32_t rank = a.pos[p];
+        if (rank == kNoTile) continue;
+        uint32_t nd[3], local;
+        double ph[3];
+        node_cell(g, a.x[p], a.y[p], a.z[p], nd, ph);
+        const uint32_t t = tile_of(a, nd, local);
+        put_record<R>(a, p, ph, local, (u64)row_sh[t] + rank, scale);
     }
 }
 
@@ -611,12 +713,21 @@ hipError_t launch_deposit_sorted(const GridDev &g, const DepSortArgs &a, int dty
     const u64 per_bin = (u64)kGridBlock * kBinItems;
     const int bin_blocks = (int)((a.cap + per_bin - 1) / per_bin);
     if (bin_blocks == 0) return hipSuccess;
-    if (a.ntiles <= kBinLdsTiles)
+    const size_t row_lds = (size_t)a.ntiles * sizeof(uint32_t);
+    if (a.rows) {
+        hipLaunchKernelGGL(k_dep_rows, dim3(kDepRows), dim3(kRowBlock), row_lds, s, g, a);
+        hipLaunchKernelGGL(k_dep_cols, dim3((a.ntiles + 63) / 64), dim3(kGridBlock), 0, s, a);
+    } else if (a.ntiles <= kBinLdsTiles) {
         hipLaunchKernelGGL(k_dep_bin<true>, dim3(bin_blocks), dim3(kGridBlock), 0, s, g, a);
-    else
+    } else {
         hipLaunchKernelGGL(k_dep_bin<false>, dim3(bin_blocks), dim3(kGridBlock), 0, s, g, a);
+    }
     hipLaunchKernelGGL(k_dep_scan, dim3(1), dim3(kScanBlock), 0, s, a);
-    if (dtype == 0)
+    if (a.rows && dtype == 0)
+        hipLaunchKernelGGL(k_dep_scatter_rows<float>, dim3(kDepRows), dim3(kRowBlock), row_lds, s, g, a);
+    else if (a.rows)
+        hipLaunchKernelGGL(k_dep_scatter_rows<double>, dim3(kDepRows), dim3(kRowBlock), row_lds, s, g, a);
+    else if (dtype == 0)
         hipLaunchKernelGGL(k_dep_scatter<float>, dim3(blocks), dim3(kGridBlock), 0, s, g, a);
     else
         hipLaunchKernelGGL(k_dep_scatter<double>, dim3(blocks), dim3(kGridBlock), 0, s, g, a);

@@ -243,6 +243,16 @@ constexpr uint32_t kDepPart = 2048;             // particles of one tile summed 
 constexpr uint32_t kDepStage = 3 * 6 * 6 * 6;   // doubles staged per part
 constexpr uint32_t kBinLdsTiles = 4096;         // up to this many tiles counted in LDS
 constexpr uint32_t kDepMaxTiles = 1u << 18;     // beyond: the wave-run kernel
+constexpr uint32_t kDepRows = 256;              // blocks of the row-wise tile count (k_dep_rows)
+constexpr uint32_t kDepRowTiles = 16384;        // up to this many tiles counted row-wise
+// Whether a deposit counts its tiles row by row.  The other way, one atomic add on the tile's
+// counter for every tile that a block of 2,048 particles touches (for every particle beyond
+// kBinLdsTiles), serves about 8 adds per ns: 249 us for 2,000,003 particles in random order on
+// 4,992 tiles, 22 row by row.  That costs 16 bytes of traffic per row and tile and two more
+// launches, so it is taken where random order would need more than 2^18 adds (33 us).
+inline bool dep_by_rows(u64 cap, u64 ntiles) {
+    return ntiles <= kDepRowTiles && (ntiles < 2048 ? ntiles : 2048) * (cap / 2048) > (1u << 18);
+}
 // parts a deposit of cap slots over ntiles tiles can need
 inline u64 dep_max_parts(u64 cap, u64 ntiles) { return ntiles + (cap + kDepPart - 1) / kDepPart; }
 // One particle of the tile-sorted deposition: one cache line.
@@ -270,6 +280,8 @@ struct DepSortArgs {
     uint32_t *pos;                  // per slot: rank in its tile (~0u: off the grid)
     DepRecord *rec;                 // cap records in tile order
     double *stage;                  // kDepStage per part: the part's summed region
+    uint32_t *rows;                 // kDepRows x ntiles, or null: counts of each row of particles, then
+                                    // the row's first place in each tile
 };
 
 // dtype: 0 = float, 1 = double (the context's momentum and field type).
