@@ -1139,6 +1139,7 @@ __device__ __forceinline__ void photon_sample(const StepArgs &a, u64 i, R kx, R 
     R dx = 0, dy = 0, dz = 0;
     bool dead = false;
     uint32_t used = 0;
+    R x = R(0.5);
     Draw<R> draw;
     for (uint32_t k = 0; k < N && !dead; ++k) {
         used = k + 1;
@@ -1147,9 +1148,8 @@ __device__ __forceinline__ void photon_sample(const StepArgs &a, u64 i, R kx, R 
         dy += diry * str;
         dz += dirz * str;
         // candidate x, test value y, acceptance against eq. (2)
-        R x, y;
+        R y;
         draw.get(k, idlo, idhi, step, klo, khi, x, y);
-        bool acc = false;
         if (y < squeeze) {
             const R xx = x * (R(1) - x);
             const R z = R(2.0 / 3.0) * rcp(chir * xx);
@@ -1158,62 +1158,66 @@ __device__ __forceinline__ void photon_sample(const StepArgs &a, u64 i, R kx, R 
             const R pp = A * (G - xx * F);
             tl.max_p = fmax(tl.max_p, pp);
             tl.clips += pp > R(1);
-            acc = y < pp;
+            dead = y < pp;
         }
-        // pair creation: electron with x eps, positron with (1-x) eps, along k; delete
-        const u64 m = __ballot(acc);
-        if (m) {
-            const int leader = __ffsll((long long)m) - 1;
-            u64 be = 0, bp = 0, bd = 0;
-            if (__lane_id() == leader) {
-                const u64 c = (u64)__popcll(m);
-                be = atomicAdd(el.n, c);
-                bp = atomicAdd(po.n, c);
-                bd = atomicAdd(&a.st->dead, c);
+    }
+    // Pair creation: electron with x eps, positron with (1-x) eps, along k, at the end of the
+    // sub-step of the decay; delete.  All photons of the group that decayed, whatever
+    // their sub-step, share one atomic on each of the three counters: taken at every
+    // sub-step with a decay these, 12 ns each on one address, were what a shower's photons
+    // waited for (65,536 photons, a third of them decaying: MEASURED).
+    const u64 m = __ballot(dead);
+    if (m) {
+        const int leader = __ffsll((long long)m) - 1;
+        u64 be = 0, bp = 0, bd = 0;
+        if (__lane_id() == leader) {
+            const u64 c = (u64)__popcll(m);
+            be = atomicAdd(el.n, c);
+            bp = atomicAdd(po.n, c);
+            bd = atomicAdd(&a.st->dead, c);
+        }
+        be = __shfl(be, leader);
+        bp = __shfl(bp, leader);
+        bd = __shfl(bd, leader);
+        if (dead) {
+            const u64 r = (u64)__popcll(m & lanemask_lt());
+            const uint32_t k = used - 1;
+            a.dead_idx[bd + r] = i;
+            const double px = x0 + (double)dx, py = y0 + (double)dy, pz = z0 + (double)dz;
+            const R w = ((const R *)sp.w)[i];
+            const double tb = ps.t0 + (double)(k + 1) * st;
+            const R ge = x * epsr, gp = (R(1) - x) * epsr;
+            const R ue = sqrt_(fmax(ge * ge - R(1), R(0)));
+            const R up = sqrt_(fmax(gp * gp - R(1), R(0)));
+            if (be + r < el.cap) {
+                const u64 j = be + r;
+                el.x[j] = px;
+                el.y[j] = py;
+                el.z[j] = pz;
+                ((R *)el.ux)[j] = ue * dirx;
+                ((R *)el.uy)[j] = ue * diry;
+                ((R *)el.uz)[j] = ue * dirz;
+                ((R *)el.w)[j] = w;
+                el.id[j] = child_id(a.seed, pid, step, k, 0);
+                if (el.parent) el.parent[j] = pid;
+                if (el.tau) el.tau[j] = -1.0;
+                if (el.birth) el.birth[j] = tb;
             }
-            be = __shfl(be, leader);
-            bp = __shfl(bp, leader);
-            bd = __shfl(bd, leader);
-            if (acc) {
-                const u64 r = (u64)__popcll(m & lanemask_lt());
-                a.dead_idx[bd + r] = i;
-                const double px = x0 + (double)dx, py = y0 + (double)dy, pz = z0 + (double)dz;
-                const R w = ((const R *)sp.w)[i];
-                const double tb = ps.t0 + (double)(k + 1) * st;
-                const R ge = x * epsr, gp = (R(1) - x) * epsr;
-                const R ue = sqrt_(fmax(ge * ge - R(1), R(0)));
-                const R up = sqrt_(fmax(gp * gp - R(1), R(0)));
-                if (be + r < el.cap) {
-                    const u64 j = be + r;
-                    el.x[j] = px;
-                    el.y[j] = py;
-                    el.z[j] = pz;
-                    ((R *)el.ux)[j] = ue * dirx;
-                    ((R *)el.uy)[j] = ue * diry;
-                    ((R *)el.uz)[j] = ue * dirz;
-                    ((R *)el.w)[j] = w;
-                    el.id[j] = child_id(a.seed, pid, step, k, 0);
-                    if (el.parent) el.parent[j] = pid;
-                    if (el.tau) el.tau[j] = -1.0;
-                    if (el.birth) el.birth[j] = tb;
-                }
-                if (bp + r < po.cap) {
-                    const u64 j = bp + r;
-                    po.x[j] = px;
-                    po.y[j] = py;
-                    po.z[j] = pz;
-                    ((R *)po.ux)[j] = up * dirx;
-                    ((R *)po.uy)[j] = up * diry;
-                    ((R *)po.uz)[j] = up * dirz;
-                    ((R *)po.w)[j] = w;
-                    po.id[j] = child_id(a.seed, pid, step, k, 1);
-                    if (po.parent) po.parent[j] = pid;
-                    if (po.tau) po.tau[j] = -1.0;
-                    if (po.birth) po.birth[j] = tb;
-                }
-                dead = true;
-                count_gap(a, 1, k + 1);
+            if (bp + r < po.cap) {
+                const u64 j = bp + r;
+                po.x[j] = px;
+                po.y[j] = py;
+                po.z[j] = pz;
+                ((R *)po.ux)[j] = up * dirx;
+                ((R *)po.uy)[j] = up * diry;
+                ((R *)po.uz)[j] = up * dirz;
+                ((R *)po.w)[j] = w;
+                po.id[j] = child_id(a.seed, pid, step, k, 1);
+                if (po.parent) po.parent[j] = pid;
+                if (po.tau) po.tau[j] = -1.0;
+                if (po.birth) po.birth[j] = tb;
             }
+            count_gap(a, 1, k + 1);
         }
     }
     // positions: the caller has written the end-of-step position (the survivor's);
