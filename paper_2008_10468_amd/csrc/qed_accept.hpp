@@ -8,6 +8,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include "qed_stage.hpp"
+
 #define QED_ACC_STORAGE static __constant__ const
 #include "accept_coeffs.inc"
 #undef QED_ACC_STORAGE
@@ -27,10 +29,9 @@ static_assert(AcceptTable::kBins == 1u << (32 - AcceptTable::kShift), "64 bins: 
 
 // Copy the table into the block's LDS copy (every thread calls; the caller's barrier follows).
 __device__ __forceinline__ void accept_stage(AcceptTable &t) {
-    const uint32_t *src = &qed_acc_t[0][0];
-    for (int i = threadIdx.x; i < AcceptTable::kRow * (int)AcceptTable::kBins / 4; i += blockDim.x)
-        (&t.t[0][0])[i] = src[i];
-    for (int i = threadIdx.x; i < AcceptTable::kRow; i += blockDim.x) t.top[i] = qed_acc_top[i] * (1.001f / 255.0f);
+    stage_copy<AcceptTable::kRow * (int)AcceptTable::kBins / 4>(&t.t[0][0], &qed_acc_t[0][0]);
+    stage_table<AcceptTable::kRow>([](int i) { return qed_acc_top[i] * (1.001f / 255.0f); },
+                                   [&](int i, float v) { t.top[i] = v; });
 }
 
 // The bound for one chi: the test value of a candidate whose word is w rejects if

@@ -835,7 +835,7 @@ struct SurrLds {
 __device__ __forceinline__ void surr_stage(const StepArgs &a, SurrLds &S) {
     if (a.model) mlp_stage(a.model, S.mlp);
     if (threadIdx.x == 0) S.have_model = a.model != nullptr;
-    rate_stage(S.rate);  // ends with a barrier
+    rate_stage(S.rate);
 }
 
 // x = delta^(1/3) from eq. (1) at fixed chi by rejection against the envelope.
@@ -1301,15 +1301,17 @@ __device__ __forceinline__ ChildPool<R> &lepton_lds_init(const StepArgs &a, Lept
         L.cb.dst = a.sp[2];
     }
     accept_stage(L.acc);
-    syn_stage(L.tab);  // ends with a block barrier
+    syn_stage(L.tab);
+    __syncthreads();
     return L.cb;
 }
 
 __device__ __forceinline__ ChildBuf &lepton_lds_init(const StepArgs &a, LeptonLds<float, true> &L) {
     auto &cb = L.cb[threadIdx.x / 64];
     if (__lane_id() == 0) cb.count = 0;
+    syn_stage(L.tab);
     surr_stage(a, L.surr);
-    syn_stage(L.tab);  // ends with a block barrier
+    __syncthreads();
     return cb;
 }
 
@@ -1541,14 +1543,13 @@ __global__ __launch_bounds__(kBlock, sizeof(R) == 4 ? kPrepassBlocks[SURR] : 4) 
     for (int b = threadIdx.x; b < kBins; b += kBlock) h[b] = 0;
     if (a.prepass_finish) {
         if constexpr (SURR) {
-            rate_stage(L.rate);  // ends with a barrier
+            rate_stage(L.rate);
         } else {
             accept_stage(L.acc);
-            syn_stage(L.tab);    // ends with a barrier
+            syn_stage(L.tab);
         }
-    } else {
-        __syncthreads();
     }
+    __syncthreads();
     Tally<R> t;
     for (u64 i = (u64)blockIdx.x * kBlock + threadIdx.x; i < n; i += (u64)gridDim.x * kBlock) {
         const Lepton<R> p = load_lepton<R>(a, s, i);
@@ -1877,6 +1878,7 @@ __global__ __launch_bounds__(kBlock) void k_photon(StepArgs a) {
     if (lo + (u64)blockIdx.x * kBlock >= n) return;
     pair_stage(pt);
     syn_stage(tab);
+    __syncthreads();
     const SpeciesDev &sp = a.sp[2];
     const FieldDev &fl = a.fl[2];
     const bool uni = fl.stride == 0;
@@ -2070,6 +2072,7 @@ __global__ __launch_bounds__(kBlock) void k_photon_surr(StepArgs a) {
     if constexpr (NET) mlp_stage(a.pair_model, net.M);
     pair_stage(pt);
     syn_stage(tab);
+    __syncthreads();
     const SpeciesDev &sp = a.sp[2];
     const SpeciesDev &el = a.sp[0];
     const SpeciesDev &po = a.sp[1];
@@ -2230,6 +2233,7 @@ __global__ __launch_bounds__(kBlock) void k_photon_surr(StepArgs a) {
 __global__ __launch_bounds__(kBlock) void k_pair_rate(const float *__restrict__ chi, float *__restrict__ out, u64 n) {
     __shared__ PairTable t;
     pair_stage(t);
+    __syncthreads();
     for (u64 i = (u64)blockIdx.x * kBlock + threadIdx.x; i < n; i += (u64)gridDim.x * kBlock)
         out[i] = pair_t(chi[i], t);
 }
@@ -2398,6 +2402,7 @@ __global__ __launch_bounds__(kBlock) void k_synchrotron(const R *__restrict__ x,
                                                         R *__restrict__ G, u64 n, DevState *st) {
     __shared__ SynTable<R> tab;
     syn_stage(tab);
+    __syncthreads();
     constexpr int V = VEC ? 16 / (int)sizeof(R) : 1;
     using Vec = typename std::conditional<sizeof(R) == 4, float4, double2>::type;
     uint32_t bad = 0;
@@ -2440,6 +2445,7 @@ __global__ __launch_bounds__(kBlock) void k_synchrotron(const R *__restrict__ x,
 __global__ __launch_bounds__(kBlock) void k_rate(const float *__restrict__ chi, float *__restrict__ out, u64 n) {
     __shared__ RateTable t;
     rate_stage(t);
+    __syncthreads();
     for (u64 i = (u64)blockIdx.x * kBlock + threadIdx.x; i < n; i += (u64)gridDim.x * kBlock)
         out[i] = rate_chi_q(chi[i], t);
 }

@@ -24,6 +24,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "qed_stage.hpp"
+
 namespace qed {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -117,13 +119,12 @@ __device__ __forceinline__ void mlp_pack(const float *__restrict__ p, MlpLds &M)
     }
 }
 
-// Copy an installed model into LDS (every thread calls; ends with a barrier).
+// Copy an installed model into LDS (every thread calls; the caller's barrier follows).
 __device__ __forceinline__ void mlp_stage(const MlpModel *__restrict__ src, MlpLds &M) {
     const uint4 *s = reinterpret_cast<const uint4 *>(src);
     uint4 *d = reinterpret_cast<uint4 *>(&M);
     static_assert(sizeof(MlpLds) % 16 == 0, "MlpLds must be a multiple of 16 bytes");
-    for (int i = threadIdx.x; i < (int)(sizeof(MlpLds) / 16); i += blockDim.x) d[i] = s[i];
-    __syncthreads();
+    stage_copy<(int)(sizeof(MlpLds) / 16)>(d, s);
 }
 
 // Per-wave scratch of the batched evaluation: the rows' inputs and outputs (up to

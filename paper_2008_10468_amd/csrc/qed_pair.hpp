@@ -8,6 +8,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include "qed_stage.hpp"
+
 #define QED_PAIR_STORAGE static __constant__ const
 #include "pair_coeffs.inc"
 #undef QED_PAIR_STORAGE
@@ -23,14 +25,11 @@ struct PairTable {
 
 static_assert(QED_PAIR_NCOEF == 7, "pair-rate kernel assumes 7 coefficients");
 
-// Copy the tables into the block's LDS copy (every thread calls; ends with a barrier).
+// Copy the tables into the block's LDS copy (every thread calls; the caller's barrier follows).
 __device__ __forceinline__ void pair_stage(PairTable &t) {
-    for (int i = threadIdx.x; i < PairTable::kSeg * 8; i += blockDim.x) {
-        const int sg = i >> 3, k = i & 7;
-        reinterpret_cast<float *>(&t.c[sg][0])[k] = k < 7 ? qed_pair_coef[sg][k] : 0.0f;
-    }
-    for (int i = threadIdx.x; i < PairTable::kSeg; i += blockDim.x) t.env[i] = qed_pair_env[i];
-    __syncthreads();
+    stage_table<PairTable::kSeg * 8>([](int i) { return (i & 7) < 7 ? qed_pair_coef[i >> 3][i & 7] : 0.0f; },
+                                  [&](int i, float v) { reinterpret_cast<float *>(&t.c[0][0])[i] = v; });
+    stage_copy<PairTable::kSeg>(t.env, qed_pair_env);
 }
 
 // T(chi) (0 for chi <= 0; the float result underflows to 0 below chi ~ 0.03, where

@@ -7,6 +7,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include "qed_stage.hpp"
+
 #define QED_RATE_STORAGE static __constant__ const
 #include "rate_coeffs.inc"
 #undef QED_RATE_STORAGE
@@ -22,14 +24,11 @@ struct RateTable {
 
 static_assert(QED_RATE_NCOEF == 7, "rate kernel assumes 7 coefficients");
 
-// Copy the tables into the block's LDS copy (every thread calls; ends with a barrier).
+// Copy the tables into the block's LDS copy (every thread calls; the caller's barrier follows).
 __device__ __forceinline__ void rate_stage(RateTable &t) {
-    for (int i = threadIdx.x; i < RateTable::kSeg * 8; i += blockDim.x) {
-        const int sg = i >> 3, k = i & 7;
-        reinterpret_cast<float *>(&t.c[sg][0])[k] = k < 7 ? qed_rate_coef[sg][k] : 0.0f;
-    }
-    for (int i = threadIdx.x; i < RateTable::kSeg; i += blockDim.x) t.env[i] = qed_rate_env[i];
-    __syncthreads();
+    stage_table<RateTable::kSeg * 8>([](int i) { return (i & 7) < 7 ? qed_rate_coef[i >> 3][i & 7] : 0.0f; },
+                                  [&](int i, float v) { reinterpret_cast<float *>(&t.c[0][0])[i] = v; });
+    stage_copy<RateTable::kSeg>(t.env, qed_rate_env);
 }
 
 // chi q(chi) for chi >= 0 (0 gives 0).  Below 2^L0, q is constant to float

@@ -10,6 +10,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include "qed_stage.hpp"
+
 #define QED_SYN_STORAGE static __constant__ const
 #include "synchro_coeffs.inc"
 #undef QED_SYN_STORAGE
@@ -42,18 +44,16 @@ struct SynTable<double> {
 static_assert(QED_SYN_F32_NCOEF == 8, "float kernel assumes 8 coefficients");
 static_assert(QED_SYN_F64_NCOEF == 12, "double kernel assumes 12 coefficients");
 
-// Copy the constant table into the block's LDS copy.  All threads of the block
-// must call it before any uses the table.
+// Copy the constant table into the block's LDS copy (every thread calls; the caller's
+// barrier follows).
 __device__ __forceinline__ void syn_stage(SynTable<float> &t) {
     const float4 *src = reinterpret_cast<const float4 *>(&qed_syn_f32_coef[0][0][0]);
-    for (int i = threadIdx.x; i < SynTable<float>::kWords / 4; i += blockDim.x) t.v[i] = src[i];
-    __syncthreads();
+    stage_copy<SynTable<float>::kWords / 4>(t.v, src);
 }
 
 __device__ __forceinline__ void syn_stage(SynTable<double> &t) {
     const double2 *src = reinterpret_cast<const double2 *>(&qed_syn_f64_coef[0][0][0]);
-    for (int i = threadIdx.x; i < SynTable<double>::kWords / 2; i += blockDim.x) t.v[i] = src[i];
-    __syncthreads();
+    stage_copy<SynTable<double>::kWords / 2>(t.v, src);
 }
 
 // Float z^(1/3) for 0 <= z <= 2^100: 2^(log2(z)/3) from the hardware log2 / exp2

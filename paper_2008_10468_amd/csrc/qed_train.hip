@@ -64,6 +64,7 @@ __global__ __launch_bounds__(kBlock) void k_cdf_table(CdfTableDev t) {
     __shared__ SynTable<double> tab;
     __shared__ double wsum[kBlock / 64];
     syn_stage(tab);
+    __syncthreads();
     const int c = blockIdx.x;
     const double l10 = t.lo10 + (t.hi10 - t.lo10) * (double)c / (double)(t.nchi - 1);
     const int per = t.nx / kBlock;  // intervals per thread
@@ -598,6 +599,7 @@ __global__ __launch_bounds__(kBlock) void k_mlp_infer(const MlpModel *model, con
     __shared__ MlpLds M;
     __shared__ MlpWave ws[kBlock / 64];
     mlp_stage(model, M);
+    __syncthreads();
     MlpWave &W = ws[threadIdx.x / 64];
     // wave-uniform trip count: every lane takes part in the matrix-core passes
     for (u64 i0 = (u64)blockIdx.x * kBlock; i0 < n; i0 += (u64)gridDim.x * kBlock) {
@@ -615,6 +617,7 @@ __global__ __launch_bounds__(kBlock) void k_mlp_validate(const MlpModel *model, 
     __shared__ MlpWave ws[kBlock / 64];
     __shared__ float wmax[kBlock / 64];
     mlp_stage(model, M);
+    __syncthreads();
     MlpWave &W = ws[threadIdx.x / 64];
     const int bin = blockIdx.x / per_bin, q = blockIdx.x % per_bin;
     const double span = 1.0 / (double)M.inv_span;
