@@ -485,6 +485,7 @@ qed_status step_impl(qed_ctx *c, qed_particles *p, const qed_field fields[3], do
     a.bins_per_octave = c->tune.bins_per_octave;
     a.light_tile = c->tune.light_tile;
     a.tiled_slots = c->tune.tiled_slots;
+    a.tile_waves = (uint32_t)c->num_cu * 8u;
     a.alive = x.alive;
     a.dead_idx = x.dead_idx;
     a.hole_idx = x.hole_idx;

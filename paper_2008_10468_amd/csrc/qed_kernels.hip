@@ -21,7 +21,7 @@
 //              first; k_light runs the light particles in tiles sorted by N; k_heavy
 //              is a persistent kernel whose waves claim chunks of the queue, so the
 //              64 lanes of a wave carry nearly the same N;
-//     tiled:   k_tiled sorts 256-slot tiles by N in LDS and runs them heaviest first;
+//     tiled:   k_tiled sorts tiles of up to 256 slots by N in LDS and runs them heaviest first;
 //   each has an instance for the lepton optical-depth path (surrogate sampler);
 //   cascade passes (cascade_generations > 0): k_gen, then k_photon and k_lepton over
 //              the particles created by the previous pass, from their birth times;
@@ -1456,7 +1456,8 @@ __device__ __forceinline__ bool finish_single(const StepArgs &a, int s, u64 i, c
 // the wave in LDS, which is run 64 particles at a time, so that their emissions and
 // network passes run with full waves instead of one or two lanes (1.05M electrons in the
 // laser field, 1.8% emitting: 73 to 60 us).  Where at least half of the 64 are left they
-// run at once, without reading their records again.  Algorithm 1's loop, whose
+// run at once, without reading their records again; so are all of a wave that has one 64
+// only (30,000 electrons: 22 to 20.5 us).  Algorithm 1's loop, whose
 // particles of two and more sub-steps are a third there, is better off without the
 // second read (54 against 61 us).
 constexpr uint32_t kLeptonQueue = 128;   // at most 63 + 31 queued
@@ -1477,6 +1478,7 @@ __global__ __launch_bounds__(kBlock, SURR ? 2 : sizeof(R) == 4 ? 4 : 3) void k_l
     if constexpr (SURR) {
         uint32_t *qslot = slot_sh[wv], *qn = n_sh[wv];   // slot - lo, sub-steps
         uint32_t queued = 0;   // wave-uniform
+        const uint32_t fill = hi - lo > G ? 32u : 0u;    // a wave of one 64 runs them at once
         for (;; i0 += G) {
             const bool more = i0 < hi;   // the last passes of the loop run what is still queued
             u64 i = i0 + lane;
@@ -1487,10 +1489,10 @@ __global__ __launch_bounds__(kBlock, SURR ? 2 : sizeof(R) == 4 ? 4 : 3) void k_l
                 const bool has = i < hi;
                 N = lepton_fetch(a, s, i, has, p, t, a.dt);
                 if (has && N == 0 && a.sp[s].events) a.sp[s].events[i] = 0;
-                if (N == 1 && finish_single<R, SURR>(a, s, i, p, L, t)) N = 0;
+                if (fill && N == 1 && finish_single<R, SURR>(a, s, i, p, L, t)) N = 0;
                 m = __ballot(N != 0);
             }
-            if (__popcll(m) < 32) {
+            if (!more || (uint32_t)__popcll(m) < fill) {
                 if (N) {
                     const uint32_t q = queued + (uint32_t)__popcll(m & lanemask_lt());
                     qslot[q] = (uint32_t)(i - lo);
@@ -1653,22 +1655,37 @@ __global__ __launch_bounds__(kBlock) void k_scatter(StepArgs a) {
     }
 }
 
-// Light pass: each wave takes tiles of a.light_tile consecutive slots (at most kTile);
-// inside a tile the light particles (1 <= N <= light_max) are counting-sorted by N
+// Light pass: each wave takes tiles of consecutive slots (tile_slots, at most
+// a.light_tile); inside a tile the light particles (1 <= N <= light_max) are counting-sorted by N
 // in the wave's LDS, heaviest first, and run 64 at a time in that order, so the
 // lanes of a wave carry nearly the same N.  Waves never wait for each other, and
 // the particle data stay in the tile's address window.
 constexpr int kTile = 512;     // largest tile (8 slots per lane)
 constexpr int kTileKeys = 64;  // N >= 63 share the heaviest key
 
+// Slots of a wave's tile, a multiple of 64 up to most: as few as give every wave of
+// a.tile_waves (two blocks per CU, which all kernels here hold at once) a tile of its own.
+// A wave runs its tile's groups of 64 one after the other, so while waves are missing
+// a smaller tile shortens the launch; once the chip holds no more, a larger one
+// sorts better and stages the tables once for more particles.  MEASURED, us for tiles of
+// 64 / 128 / 256 (/ 512): k_tiled, ring, 100,000: 50 / 72 / 118, 200,000: 81 / 78 / 119,
+// 400,000: 116 / 128 / 130, 1M: 233 / 213 / 232; spot, 1M: 953 / 622 / 454; k_light,
+// laser, 30,000: 19 / 21 / 26 / 33, 200,000: 39 / 25 / 27 / 35, 1M: 78 / 64 / 59 / 61.
+__device__ __forceinline__ uint32_t tile_slots(const StepArgs &a, u64 n, uint32_t most) {
+    if (n >= (u64)most * a.tile_waves) return most;
+    const uint32_t fair = ((uint32_t)n + a.tile_waves - 1u) / a.tile_waves;
+    return min((fair + 63u) & ~63u, most);
+}
+
 template <class R, bool SURR>
-__global__ __launch_bounds__(kBlock) void k_light(StepArgs a) {
+__global__ __launch_bounds__(kBlock, SURR ? 2 : 3) void k_light(StepArgs a) {
     __shared__ LeptonLds<R, SURR> L;
     __shared__ uint32_t hist_sh[kBlock / 64][kTileKeys];
     __shared__ uint16_t order_sh[kBlock / 64][kTile];
     const int s = blockIdx.y;
     const u64 n = a.st->n0[s];
-    if ((u64)blockIdx.x * (kBlock / 64) * a.light_tile >= n) return;
+    const uint32_t tile = tile_slots(a, n, a.light_tile), qn = tile / 64;
+    if ((u64)blockIdx.x * (kBlock / 64) * tile >= n) return;
     auto &cb = lepton_lds_init(a, L);
     const uint32_t lmax = a.light_max;
     const uint32_t lane = __lane_id();
@@ -1676,7 +1693,6 @@ __global__ __launch_bounds__(kBlock) void k_light(StepArgs a) {
     uint32_t *hist = hist_sh[wv];
     uint16_t *order = order_sh[wv];
     const u64 nwaves = (u64)gridDim.x * (kBlock / 64);
-    const uint32_t tile = a.light_tile, qn = tile / 64;
     Tally<R> t;
     for (u64 t0 = ((u64)blockIdx.x * (kBlock / 64) + wv) * tile; t0 < n; t0 += nwaves * tile) {
         hist[lane] = 0;
@@ -1720,46 +1736,53 @@ __global__ __launch_bounds__(kBlock) void k_light(StepArgs a) {
     flush_tally(t, a.st, s);
 }
 
-// Tile-sorted scheduler (one pass, no pre-pass): each wave takes tiles of kTiledSlots
-// consecutive slots, computes every particle's sub-step count, counting-sorts the
-// tile by it in LDS (heaviest first) and runs the tile 64 particles at a time in
-// that order, so the lanes of a wave carry nearly the same N.  The particle
-// records are read twice, the second time from the cache.  Tiles hold a.tiled_slots
-// slots, at most kTiledSlots.
+// Tile-sorted scheduler (one pass, no pre-pass): each wave takes tiles of consecutive
+// slots (tile_slots, at most a.tiled_slots), computes every particle's sub-step count,
+// counting-sorts the tile by it in LDS (heaviest first) and runs the tile 64 particles at
+// a time in that order, so the lanes of a wave carry nearly the same N.  The particle
+// records are read twice, the second time from the cache.  On the optical-depth path the
+// particles of a single quiet sub-step end while they are counted (1M electrons of the
+// laser field: 162 to 65 us with the resolves of full waves that this leaves; 200,000:
+// 51 to 28); Algorithm 1's own loop is as fast with them (66 us with it, 61 without).
 constexpr int kTiledSlots = 256;  // largest wave tile of the tile-sorted scheduler (4 slots per lane)
 
+__device__ __forceinline__ uint32_t tile_key(uint32_t N) {
+    return kTileKeys - (N < kTileKeys - 1 ? N : kTileKeys - 1);
+}
+
 template <class R, bool SURR>
-__global__ __launch_bounds__(kBlock) void k_tiled(StepArgs a) {
+__global__ __launch_bounds__(kBlock, !SURR && sizeof(R) == 4 ? 3 : 2) void k_tiled(StepArgs a) {
     __shared__ LeptonLds<R, SURR> L;
     __shared__ uint32_t hist_sh[kBlock / 64][kTileKeys];
     __shared__ uint16_t order_sh[kBlock / 64][kTiledSlots];
     __shared__ uint32_t nsub_sh[kBlock / 64][kTiledSlots];
+    __shared__ uint16_t rank_sh[kBlock / 64][kTiledSlots];
     const int s = blockIdx.y;
     const u64 n = a.st->n0[s];
-    if ((u64)blockIdx.x * (kBlock / 64) * a.tiled_slots >= n) return;
+    const uint32_t tile = tile_slots(a, n, a.tiled_slots);
+    if ((u64)blockIdx.x * (kBlock / 64) * tile >= n) return;
     auto &cb = lepton_lds_init(a, L);
     const uint32_t lane = __lane_id();
     const int wv = threadIdx.x / 64;
     uint32_t *hist = hist_sh[wv];
     uint16_t *order = order_sh[wv];
     uint32_t *nsub = nsub_sh[wv];
+    uint16_t *rank = rank_sh[wv];   // within the slots of the same key
     const u64 nwaves = (u64)gridDim.x * (kBlock / 64);
-    const uint32_t tile = a.tiled_slots, qn = tile / 64;
     Tally<R> t;
     for (u64 t0 = ((u64)blockIdx.x * (kBlock / 64) + wv) * tile; t0 < n; t0 += nwaves * tile) {
         hist[lane] = 0;
         __syncwarp();
-        uint32_t kr[kTiledSlots / 64];  // key << 16 | rank
-#pragma unroll
-        for (int q = 0; q < kTiledSlots / 64; ++q) {
-            const u64 i = t0 + q * 64 + lane;
-            const bool in = (uint32_t)q < qn && i < n;
+#pragma unroll 1
+        for (uint32_t q = 0; q < tile; q += 64) {
+            const u64 i = t0 + q + lane;
+            const bool in = i < n;
             Lepton<R> p;
-            const uint32_t N = lepton_fetch(a, s, i, in, p, t, a.dt);
+            uint32_t N = lepton_fetch(a, s, i, in, p, t, a.dt);
             if (in && N == 0 && a.sp[s].events) a.sp[s].events[i] = 0;
-            nsub[q * 64 + lane] = N;
-            const uint32_t key = N ? kTileKeys - (N < kTileKeys - 1 ? N : kTileKeys - 1) : 0u;
-            kr[q] = key ? (key << 16) | atomicAdd(&hist[key], 1u) : 0u;
+            if (SURR && N == 1 && finish_single<R, SURR>(a, s, i, p, L, t)) N = 0;
+            nsub[q + lane] = N;
+            if (N) rank[q + lane] = (uint16_t)atomicAdd(&hist[tile_key(N)], 1u);
         }
         __syncwarp();
         const uint32_t h = lane >= 1 ? hist[lane] : 0u;
@@ -1773,9 +1796,8 @@ __global__ __launch_bounds__(kBlock) void k_tiled(StepArgs a) {
         __syncwarp();
         hist[lane] = incl - h;
         __syncwarp();
-#pragma unroll
-        for (int q = 0; q < kTiledSlots / 64; ++q)
-            if (kr[q]) order[hist[kr[q] >> 16] + (kr[q] & 0xFFFFu)] = (uint16_t)(q * 64 + lane);
+        for (uint32_t q = lane; q < tile; q += 64)
+            if (nsub[q]) order[hist[tile_key(nsub[q])] + rank[q]] = (uint16_t)q;
         __syncwarp();
         for (uint32_t p0 = 0; p0 < total; p0 += 64) {
             const uint32_t p = p0 + lane;
