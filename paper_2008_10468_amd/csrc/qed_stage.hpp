@@ -12,7 +12,7 @@ constexpr int kStageBlock = 256;   // threads of every block that stages a table
 //
 // What bounds a short launch here is the latency of the reads, a few hundred ns each,
 // so all of a thread's reads are in flight before its first write, without a branch
-// (a thread past the end repeats the last element), and the tables of a kernel follow
+// (a thread past the end reads the last element again), and the tables of a kernel follow
 // each other without barriers: the network, the fits and the rate table (45 KB) in
 // one trip instead of ten.  30,000 electrons and 7,500 photons of the laser field: k_lepton of
 // the optical-depth path 20.6 to 19.2 us, k_photon 15.6 to 14.0.
@@ -23,7 +23,8 @@ __device__ __forceinline__ void stage_table(Get get, Put put) {
 #pragma unroll
     for (int q = 0; q < K; ++q) v[q] = get(min((int)threadIdx.x + q * kStageBlock, N - 1));
 #pragma unroll
-    for (int q = 0; q < K; ++q) put(min((int)threadIdx.x + q * kStageBlock, N - 1), v[q]);
+    for (int q = 0; q < K; ++q)
+        if ((int)threadIdx.x + q * kStageBlock < N) put((int)threadIdx.x + q * kStageBlock, v[q]);
 }
 
 template <int N, class T>
