@@ -349,7 +349,7 @@ bool table_args_ok(double lo, double hi, uint32_t nchi, uint32_t nx) {
 }
 
 qed_status build_table(qed_ctx *c, DevBufs &B, double lo, double hi, uint32_t nchi, uint32_t nx,
-                       qed::CdfTableDev &t, int kind = 0) {
+                       qed::CdfTableDev &t, int kind = 0, bool index = false) {
     t.kind = kind;
     t.nchi = (int)nchi;
     t.nx = (int)nx;
@@ -357,6 +357,8 @@ qed_status build_table(qed_ctx *c, DevBufs &B, double lo, double hi, uint32_t nc
     t.hi10 = hi;
     if (!B.alloc(&t.cdf, (size_t)nchi * (nx + 1) * sizeof(double)) || !B.alloc(&t.total, nchi * sizeof(double)))
         return QED_ERR_HIP;
+    t.index = nullptr;
+    if (index && !B.alloc(&t.index, (size_t)nchi * qed::kCdfIndex * sizeof(double))) return QED_ERR_HIP;
     if (qed::launch_cdf_table(t, c->stream) != hipSuccess) return QED_ERR_HIP;
     return QED_OK;
 }
@@ -1153,7 +1155,7 @@ qed_status qed_train_sampler(qed_ctx *c, const qed_train_config *cfg, const floa
     DevBufs B;
     qed::CdfTableDev t;
     qed_status st =
-        build_table(c, B, cfg->log10_chi_lo, cfg->log10_chi_hi, cfg->table_chi, cfg->table_x, t, cfg->target);
+        build_table(c, B, cfg->log10_chi_lo, cfg->log10_chi_hi, cfg->table_chi, cfg->table_x, t, cfg->target, true);
     if (st != QED_OK) return st;
     const u64 batch = (u64)cfg->blocks * 64 * cfg->batch_tiles;
     float *params, *m, *v, *partials, *loss, *bin_err;

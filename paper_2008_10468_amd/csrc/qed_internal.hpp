@@ -170,8 +170,11 @@ hipError_t launch_kernel(int id, const StepArgs &a, int precision, int blocks, h
 // CDF of the emitted energy over x in [0, 1] on a grid of chi: row c (chi =
 // 10^(lo10 + c (hi10 - lo10) / (nchi - 1))) holds nx + 1 values at
 // x = 1 - (1 - k/nx)^2; total[c] is the integral of eq. (1) over c b.
+constexpr int kCdfIndex = 272;   // doubles of a row's index: 17 lines of 128 bytes
+
 struct CdfTableDev {
     double *cdf;
+    double *index;  // [nchi][kCdfIndex], the first eight levels of every row's bisection, or null
     double *total;
     int nchi, nx;
     double lo10, hi10;
