@@ -1161,7 +1161,8 @@ qed_status qed_train_sampler(qed_ctx *c, const qed_train_config *cfg, const floa
     float *params, *m, *v, *partials, *loss, *bin_err;
     qed::Sample *data;
     qed::MlpModel *model;
-    if (!B.alloc(&params, QED_MLP_NPARAMS * sizeof(float)) || !B.alloc(&m, QED_MLP_NPARAMS * sizeof(float)) ||
+    char *weights;
+    if (!B.alloc(&weights, qed::kTrainWeightBytes) || !B.alloc(&params, QED_MLP_NPARAMS * sizeof(float)) || !B.alloc(&m, QED_MLP_NPARAMS * sizeof(float)) ||
         !B.alloc(&v, QED_MLP_NPARAMS * sizeof(float)) ||
         !B.alloc(&partials, (size_t)cfg->blocks * (QED_MLP_NPARAMS + 1) * sizeof(float)) ||
         !B.alloc(&loss, cfg->steps * sizeof(float)) || !B.alloc(&bin_err, cfg->nbins * sizeof(float)) ||
@@ -1176,6 +1177,7 @@ qed_status qed_train_sampler(qed_ctx *c, const qed_train_config *cfg, const floa
     HIP_TRY(hipMemsetAsync(m, 0, QED_MLP_NPARAMS * sizeof(float), c->stream));
     HIP_TRY(hipMemsetAsync(v, 0, QED_MLP_NPARAMS * sizeof(float), c->stream));
     HIP_TRY(hipMemsetAsync(bin_err, 0, cfg->nbins * sizeof(float), c->stream));
+    if (qed::launch_train_pack(params, weights, c->stream) != hipSuccess) return QED_ERR_HIP;
     const double beta1 = 0.9, beta2 = 0.999;
     const int data_blocks = grid_for(batch, c->num_cu * 8);
     for (uint32_t k = 0; k < cfg->steps; ++k) {
@@ -1184,6 +1186,7 @@ qed_status qed_train_sampler(qed_ctx *c, const qed_train_config *cfg, const floa
             return QED_ERR_HIP;
         qed::TrainArgs ta;
         ta.params = params;
+        ta.weights = weights;
         ta.batch = data;
         ta.partials = partials;
         ta.tiles = cfg->batch_tiles;
@@ -1196,6 +1199,7 @@ qed_status qed_train_sampler(qed_ctx *c, const qed_train_config *cfg, const floa
         ra.params = params;
         ra.m = m;
         ra.v = v;
+        ra.weights = weights;
         ra.loss_out = loss + k;
         const double frac = cfg->steps > 1 ? (double)k / (double)(cfg->steps - 1) : 1.0;
         ra.lr = (float)(cfg->lr_final + 0.5 * (cfg->lr - cfg->lr_final) * (1.0 + cos(M_PI * frac)));
@@ -1241,7 +1245,8 @@ qed_status qed_mlp_gradient(qed_ctx *c, const float *params, const float *sample
     const int blocks = (int)(n / 64);
     float *dp, *partials, *grad, *loss;
     qed::Sample *data;
-    if (!B.alloc(&dp, QED_MLP_NPARAMS * sizeof(float)) ||
+    char *weights;
+    if (!B.alloc(&weights, qed::kTrainWeightBytes) || !B.alloc(&dp, QED_MLP_NPARAMS * sizeof(float)) ||
         !B.alloc(&partials, (size_t)blocks * (QED_MLP_NPARAMS + 1) * sizeof(float)) ||
         !B.alloc(&grad, QED_MLP_NPARAMS * sizeof(float)) || !B.alloc(&loss, sizeof(float)) ||
         !B.alloc(&data, n * sizeof(qed::Sample)))
@@ -1249,7 +1254,9 @@ qed_status qed_mlp_gradient(qed_ctx *c, const float *params, const float *sample
     HIP_TRY(hipMemcpy(dp, params, QED_MLP_NPARAMS * sizeof(float), hipMemcpyHostToDevice));
     HIP_TRY(hipMemcpy(data, samples, n * sizeof(qed::Sample), hipMemcpyHostToDevice));
     qed::TrainArgs ta;
+    if (qed::launch_train_pack(dp, weights, c->stream) != hipSuccess) return QED_ERR_HIP;
     ta.params = dp;
+    ta.weights = weights;
     ta.batch = data;
     ta.partials = partials;
     ta.tiles = 1;

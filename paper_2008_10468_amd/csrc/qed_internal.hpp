@@ -186,8 +186,11 @@ struct Sample {
     float s, v, y, w;  // network inputs, target output, loss weight
 };
 
+constexpr size_t kTrainWeightBytes = 6 * 8192;   // the two 64 x 64 layers as matrix operands
+
 struct TrainArgs {
     const float *params;   // float parameters (kMlpParams)
+    const void *weights;   // the same weights as matrix operands (launch_train_pack)
     const Sample *batch;   // blocks * 4 waves * tiles * 16 samples
     float *partials;       // [blocks][kMlpParams + 1]: gradient sums and the loss
     uint32_t tiles;        // 16-sample tiles per wave
@@ -198,6 +201,7 @@ struct ReduceArgs {
     const float *partials;
     int blocks;
     float *params, *m, *v;  // Adam state (unused when grad_out is set)
+    void *weights;          // the updated weights as matrix operands
     float *grad_out;        // non-null: write the summed gradient, no update
     float *loss_out;        // optional: the summed loss
     float lr, beta1, beta2, eps, c1, c2;  // c1 = 1/(1-beta1^t), c2 = 1/(1-beta2^t)
@@ -209,6 +213,7 @@ hipError_t launch_cdf_table(const CdfTableDev &t, hipStream_t s);
 hipError_t launch_mlp_data(const CdfTableDev &t, Sample *out, u64 n, uint64_t seed, uint32_t step,
                            double lo10, double hi10, int blocks, hipStream_t s);
 hipError_t launch_mlp_train(const TrainArgs &ta, int blocks, hipStream_t s);
+hipError_t launch_train_pack(const float *params, void *weights, hipStream_t s);
 hipError_t launch_mlp_reduce(const ReduceArgs &ra, hipStream_t s);
 hipError_t launch_mlp_pack(const float *params, MlpModel *out, hipStream_t s);
 hipError_t launch_mlp_validate(const MlpModel *model, const CdfTableDev &t, int nbins, int per_bin,

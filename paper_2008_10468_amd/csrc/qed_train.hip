@@ -229,324 +229,319 @@ __global__ __launch_bounds__(kBlock) void k_mlp_data(CdfTableDev t, Sample *out,
 }
 
 // ---------------------------------------------------------------------------
-// Training step: forward and backward passes of 16-sample tiles per wave.
+// Training step.
 // ---------------------------------------------------------------------------
-struct alignas(16) TrainWave {
-    float s[16], v[16], yt[16], wt[16];
-    uint16_t h[16][72];   // high parts (and single bf16 values of the backward pass)
-    uint16_t l[16][72];   // residuals of the forward activations
+// Two waves share a tile of 16 samples, wave n the hidden units 32 n .. 32 n + 31 of
+// every layer, and a block has four such groups, each with its own tiles.
+constexpr int kTrainGroups = 4;
+constexpr int kTrainBlock = kTrainGroups * 128;
+
+// The waves of a group hand each other their units' values here: activations of layers
+// 1 and 2 split into high parts and residuals (A operand: row = sample) and, for
+// the weight gradients, the high parts with the samples of a unit side by side (B
+// operand); the third layer's activations; the gradients dz of layers 3 and 2.  Every
+// array has its own space, so a tile takes five barriers and no array is written
+// before the barrier after its last reader.
+struct alignas(16) TrainTile {
+    uint16_t h[2][16][72], l[2][16][72], z[2][16][72];
+    uint16_t ht[2][kHid][20];
+    float h3[16][68];
+    alignas(16) Sample sample[2][16];   // of this tile and the next
 };
 
-struct TrainParams {
-    float w1[kHid][2];
-    float b1[kHid], b2[kHid], b3[kHid], w4[kHid];
-    float b4;
+// The weights as B operands, 16 bytes per lane: tf[layer][n][kk][lane] holds
+// W[16 n + r][32 kk + kidx(g, j)] (high parts; tl the residuals), and wt the transposed
+// weights W[32 kk + kidx(g, j)][16 n + r] for dZ W.  k_mlp_reduce keeps it current.
+struct TrainWeights {
+    uint4 tf[2][4][2][64], tl[2][4][2][64], wt[2][4][2][64];
 };
+static_assert(sizeof(TrainWeights) == kTrainWeightBytes, "the buffer the host allocates");
 
-// Training layout (activations as the A operand, weights as B): tf2[n][kk][lane]
-// holds W2[16 n + r][32 kk + kidx(g, j)] (high parts; tl2 the residuals), and
-// wt2 the transposed weights W2[32 kk + kidx(g, j)][16 n + r] for dZ W.
-struct TrainLds {
-    TrainParams P;
-    uint4 tf2[4][2][64], tf3[4][2][64];
-    uint4 tl2[4][2][64], tl3[4][2][64];
-    uint4 wt2[4][2][64], wt3[4][2][64];
-    TrainWave ws[kBlock / 64];
-    float red[kMlpParams + 1];
-};
-
-__device__ __forceinline__ void pack_train(const float *__restrict__ p, TrainLds &L) {
-    for (int i = threadIdx.x; i < kHid; i += blockDim.x) {
-        L.P.w1[i][0] = p[kOffW1 + 2 * i];
-        L.P.w1[i][1] = p[kOffW1 + 2 * i + 1];
-        L.P.b1[i] = p[kOffB1 + i];
-        L.P.b2[i] = p[kOffB2 + i];
-        L.P.b3[i] = p[kOffB3 + i];
-        L.P.w4[i] = p[kOffW4 + i];
-    }
-    if (threadIdx.x == 0) L.P.b4 = p[kOffB4];
-    for (int e = threadIdx.x; e < 2 * 4 * 2 * 64; e += blockDim.x) {
-        const int lane = e & 63, kk = (e >> 6) & 1, n = (e >> 7) & 3, layer = e >> 9;
-        const int r = lane & 15, g = lane >> 4;
-        const float *W = p + (layer ? kOffW3 : kOffW2);
-        float f[8], t[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            f[j] = W[(16 * n + r) * kHid + 32 * kk + kidx(g, j)];
-            t[j] = W[(32 * kk + kidx(g, j)) * kHid + 16 * n + r];
-        }
-        (layer ? L.tf3 : L.tf2)[n][kk][lane] =
-            make_uint4(pack2(f[0], f[1]), pack2(f[2], f[3]), pack2(f[4], f[5]), pack2(f[6], f[7]));
-        (layer ? L.tl3 : L.tl2)[n][kk][lane] =
-            make_uint4(pack2_lo(f[0], f[1]), pack2_lo(f[2], f[3]), pack2_lo(f[4], f[5]), pack2_lo(f[6], f[7]));
-        (layer ? L.wt3 : L.wt2)[n][kk][lane] =
-            make_uint4(pack2(t[0], t[1]), pack2(t[2], t[3]), pack2(t[4], t[5]), pack2(t[6], t[7]));
-    }
+// Weight p, value v, into its three places.
+__device__ __forceinline__ void pack_weight(TrainWeights *t, int p, float v) {
+    const int layer = p >= kOffW3, q = p - (layer ? kOffW3 : kOffW2);
+    if (q < 0 || q >= kHid * kHid) return;
+    const int o = q / kHid, i = q % kHid;
+    uint16_t *tf = reinterpret_cast<uint16_t *>(&t->tf[layer][o >> 4][i >> 5][((i >> 3) & 3) * 16 + (o & 15)]);
+    uint16_t *tl = reinterpret_cast<uint16_t *>(&t->tl[layer][o >> 4][i >> 5][((i >> 3) & 3) * 16 + (o & 15)]);
+    uint16_t *wt = reinterpret_cast<uint16_t *>(&t->wt[layer][i >> 4][o >> 5][((o >> 3) & 3) * 16 + (i & 15)]);
+    tf[i & 7] = bf_bits(v);
+    tl[i & 7] = bf_bits(bf_res(v));
+    wt[o & 7] = bf_bits(v);
 }
 
-// A-operand fragments (high and low parts) of row r, K chunks 0 and 1.
-struct AFrag {
-    bf16x8 h0, h1, l0, l1;
-};
-
-// [16 x 64] x [64 x 64] product of split activations (A) with split weights (B):
-// hi*hi + hi*lo + lo*hi, small terms first.
-__device__ __forceinline__ void gemm_split(const AFrag &a, const uint4 (*fh)[2][64], const uint4 (*fl)[2][64],
-                                           int lane, f32x4 *acc) {
-#pragma unroll
-    for (int n = 0; n < 4; ++n) {
-        const bf16x8 b0 = as_bf8(fh[n][0][lane]), b1 = as_bf8(fh[n][1][lane]);
-        const bf16x8 c0 = as_bf8(fl[n][0][lane]), c1 = as_bf8(fl[n][1][lane]);
-        f32x4 c = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.l0, b0, c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.l1, b1, c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.h0, c0, c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.h1, c1, c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.h0, b0, c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.h1, b1, c, 0, 0, 0);
-        acc[n] = c;
-    }
+__global__ __launch_bounds__(kBlock) void k_train_pack(const float *params, TrainWeights *t) {
+    const int p = blockIdx.x * kBlock + threadIdx.x;
+    if (p < kMlpParams) pack_weight(t, p, params[p]);
 }
 
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 
-__device__ __forceinline__ s16x4 pack4(const float *v) {
-    const uint2 u = make_uint2(pack2(v[0], v[1]), pack2(v[2], v[3]));
-    return __builtin_bit_cast(s16x4, u);
+__device__ __forceinline__ uint2 pack4(const float *v) { return make_uint2(pack2(v[0], v[1]), pack2(v[2], v[3])); }
+
+// Sum over the 16 lanes of a row, in every lane: the partners are lane ^ 1, ^ 2, ^ 4 and ^ 8
+// (the mirrored lane holds what lane ^ 4 or ^ 8 does, as the lanes between are equal by then).
+__device__ __forceinline__ float row_sum(float v) {
+    auto add = [&](int other) { v += __builtin_bit_cast(float, other); };
+    const auto bits = [&] { return __builtin_bit_cast(int, v); };
+    add(__builtin_amdgcn_update_dpp(0, bits(), 0xB1, 0xF, 0xF, true));    // quad_perm 1 0 3 2
+    add(__builtin_amdgcn_update_dpp(0, bits(), 0x4E, 0xF, 0xF, true));    // quad_perm 2 3 0 1
+    add(__builtin_amdgcn_update_dpp(0, bits(), 0x141, 0xF, 0xF, true));   // row_half_mirror
+    add(__builtin_amdgcn_update_dpp(0, bits(), 0x140, 0xF, 0xF, true));   // row_mirror
+    return v;
 }
 
-// C-layout activations (rows 4g + q of column 16 n + r) -> split A-layout fragments.
-__device__ __forceinline__ AFrag transpose_split(TrainWave &W, const float (*v)[4], int r, int g) {
-    __syncwarp();
+// Forward and backward passes, a group's tiles one after the other.  Lane (r, g) of a wave
+// holds the values of its units 32 n + r and 32 n + 16 + r for the samples 4 g .. 4 g + 3
+// (the C layout of the matrix core).  Bound by latency and by the instructions of the
+// activations: with one wave for all 64 units a SIMD held a single wave (340 registers),
+// which issues at half the rate, and fetched every tile's samples only when it came to it:
+// 65,536 samples took 31.2 us; two waves to a SIMD, with the forward weights in registers,
+// the transposed ones in LDS (250 registers), take 19.7, 2.8 of them for each
+// tile of 16 per wave pair.  Four waves (16 units each) leave no registers for
+// weights, and reading these from the LDS in every tile then bounds: 21.4 us.  The
+// operations on a value and their order are those of a wave that has all units.
+__global__ __launch_bounds__(kTrainBlock) void k_mlp_train(TrainArgs ta) {
+    constexpr int kRed = kMlpParams + 1;
+    __shared__ union Lds {
+        struct {
+            TrainTile tile[kTrainGroups];
+            float w4[kHid];
+            uint4 wt[2][4][2][64];
+        } t;
+        float red[kTrainGroups][kRed];
+    } L;
+    const int lane = __lane_id(), r = lane & 15, g = lane >> 4;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), grp = wv >> 1, n = wv & 1;
+    TrainTile &T = L.t.tile[grp];
+    const float *P = ta.params;
+    const TrainWeights &K = *reinterpret_cast<const TrainWeights *>(ta.weights);
+    uint4 fh[2][2][2], fl[2][2][2];   // [layer][m][kk], m: the wave's first or second 16 units
 #pragma unroll
-    for (int n = 0; n < 4; ++n)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const __bf16 hb = (__bf16)v[n][q];
-            W.h[4 * g + q][16 * n + r] = __builtin_bit_cast(uint16_t, hb);
-            W.l[4 * g + q][16 * n + r] = bf_bits(v[n][q] - (float)hb);
-        }
-    __syncwarp();
-    AFrag a;
-    a.h0 = as_bf8(*reinterpret_cast<const uint4 *>(&W.h[r][kidx(g, 0)]));
-    a.h1 = as_bf8(*reinterpret_cast<const uint4 *>(&W.h[r][32 + kidx(g, 0)]));
-    a.l0 = as_bf8(*reinterpret_cast<const uint4 *>(&W.l[r][kidx(g, 0)]));
-    a.l1 = as_bf8(*reinterpret_cast<const uint4 *>(&W.l[r][32 + kidx(g, 0)]));
-    __syncwarp();
-    return a;
-}
-
-// C-layout tile values -> single bf16 A-layout fragments via LDS (backward pass).
-__device__ __forceinline__ void transpose_to_a(TrainWave &W, const float (*v)[4], int r, int g, bf16x8 &a0,
-                                               bf16x8 &a1) {
-    __syncwarp();
-#pragma unroll
-    for (int n = 0; n < 4; ++n)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) W.h[4 * g + q][16 * n + r] = bf_bits(v[n][q]);
-    __syncwarp();
-    a0 = as_bf8(*reinterpret_cast<const uint4 *>(&W.h[r][kidx(g, 0)]));
-    a1 = as_bf8(*reinterpret_cast<const uint4 *>(&W.h[r][32 + kidx(g, 0)]));
-    __syncwarp();
-}
-
-__device__ __forceinline__ void gemm_64(bf16x8 a0, bf16x8 a1, const uint4 (*frag)[2][64], int lane,
-                                        f32x4 *acc) {
-#pragma unroll
-    for (int n = 0; n < 4; ++n) {
-        acc[n] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-        acc[n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0, as_bf8(frag[n][0][lane]), acc[n], 0, 0, 0);
-        acc[n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1, as_bf8(frag[n][1][lane]), acc[n], 0, 0, 0);
+    for (int k = 0; k < 8; ++k) {
+        const int layer = k >> 2, m = (k >> 1) & 1, kk = k & 1;
+        fh[layer][m][kk] = K.tf[layer][2 * n + m][kk][lane];
+        fl[layer][m][kk] = K.tl[layer][2 * n + m][kk][lane];
     }
-}
+    const uint4 t0 = (&K.wt[0][0][0][0])[threadIdx.x], t1 = (&K.wt[0][0][0][0])[kTrainBlock + threadIdx.x];
+    (&L.t.wt[0][0][0][0])[threadIdx.x] = t0;
+    (&L.t.wt[0][0][0][0])[kTrainBlock + threadIdx.x] = t1;
+    if (threadIdx.x < kHid) L.t.w4[threadIdx.x] = P[kOffW4 + threadIdx.x];   // a barrier follows in every tile
+    const float b4 = P[kOffB4];
+    float w10[2], w11[2], b1[2], b2[2], b3[2], w4[2];
+    f32x4 gw2[2][4], gw3[2][4];
+    float gw10[2], gw11[2], gb1[2], gb2[2], gb3[2], gw4[2], gb4 = 0.0f, loss = 0.0f;
+#pragma unroll
+    for (int m = 0; m < 2; ++m) {
+        const int u = 32 * n + 16 * m + r;
+        w10[m] = P[kOffW1 + 2 * u];
+        w11[m] = P[kOffW1 + 2 * u + 1];
+        b1[m] = P[kOffB1 + u];
+        b2[m] = P[kOffB2 + u];
+        b3[m] = P[kOffB3 + u];
+        w4[m] = P[kOffW4 + u];
+        gw10[m] = gw11[m] = gb1[m] = gb2[m] = gb3[m] = gw4[m] = 0.0f;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) gw2[m][k] = gw3[m][k] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    }
 
-__global__ __launch_bounds__(kBlock) void k_mlp_train(TrainArgs ta) {
-    __shared__ TrainLds L;
-    for (int i = threadIdx.x; i <= kMlpParams; i += kBlock) L.red[i] = 0.0f;
-    pack_train(ta.params, L);
+    // this wave's units of layer k's activations, for the other wave
+    auto share = [&](int k, const float (*v)[4]) {
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+            const int u = 32 * n + 16 * m + r;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                T.h[k][4 * g + q][u] = bf_bits(v[m][q]);
+                T.l[k][4 * g + q][u] = bf_bits(bf_res(v[m][q]));
+            }
+            *reinterpret_cast<uint2 *>(&T.ht[k][u][4 * g]) = pack4(v[m]);
+        }
+    };
+    auto rows = [&](const uint16_t (*m)[72], int kk) {
+        return as_bf8(*reinterpret_cast<const uint4 *>(&m[r][32 * kk + kidx(g, 0)]));
+    };
+    // [16 x 64] x [64 x 32] product of layer k's split activations with split weights:
+    // hi*hi + hi*lo + lo*hi, small terms first
+    auto forward = [&](int k, f32x4 *acc) {
+        const bf16x8 h0 = rows(T.h[k], 0), h1 = rows(T.h[k], 1), l0 = rows(T.l[k], 0), l1 = rows(T.l[k], 1);
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+            const bf16x8 p0 = as_bf8(fh[k][m][0]), p1 = as_bf8(fh[k][m][1]);
+            f32x4 c = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+            c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(l0, p0, c, 0, 0, 0);
+            c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(l1, p1, c, 0, 0, 0);
+            c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(h0, as_bf8(fl[k][m][0]), c, 0, 0, 0);
+            c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(h1, as_bf8(fl[k][m][1]), c, 0, 0, 0);
+            c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(h0, p0, c, 0, 0, 0);
+            acc[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(h1, p1, c, 0, 0, 0);
+        }
+    };
+    // dZ W of the dz in z[k] (0: layer 3, 1: layer 2)
+    auto backward = [&](int k, f32x4 *acc) {
+        const bf16x8 z0 = rows(T.z[k], 0), z1 = rows(T.z[k], 1);
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+            f32x4 c = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+            c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(z0, as_bf8(L.t.wt[1 - k][2 * n + m][0][lane]), c, 0, 0, 0);
+            acc[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(z1, as_bf8(L.t.wt[1 - k][2 * n + m][1][lane]), c, 0, 0, 0);
+        }
+    };
+    // dz for the other wave, and dW += dz^T h of layer k's activations (K = the 16 samples)
+    auto weight_grad = [&](int z, const float (*dz)[4], int k, f32x4 (*acc)[4]) {
+        s16x4 ad[2];
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+            ad[m] = __builtin_bit_cast(s16x4, pack4(dz[m]));
+#pragma unroll
+            for (int q = 0; q < 4; ++q) T.z[z][4 * g + q][32 * n + 16 * m + r] = bf_bits(dz[m][q]);
+        }
+#pragma unroll
+        for (int cj = 0; cj < 4; ++cj) {
+            const s16x4 h = __builtin_bit_cast(s16x4, *reinterpret_cast<const uint2 *>(&T.ht[k][16 * cj + r][4 * g]));
+#pragma unroll
+            for (int m = 0; m < 2; ++m)
+                acc[m][cj] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ad[m], h, acc[m][cj], 0, 0, 0);
+        }
+    };
+
+    const Sample *batch = ta.batch + ((u64)blockIdx.x * kTrainGroups + grp) * (u64)ta.tiles * 16;
+    if (n == 0 && lane < 16) T.sample[0][lane] = batch[lane];
     __syncthreads();
-    const TrainParams &M = L.P;
-    const int lane = __lane_id(), r = lane & 15, g = lane >> 4, wv = threadIdx.x / 64;
-    TrainWave &W = L.ws[wv];
-    f32x4 gw2[16], gw3[16];
-#pragma unroll
-    for (int k = 0; k < 16; ++k) gw2[k] = gw3[k] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-    float gw1[4][2] = {}, gb1[4] = {}, gb2[4] = {}, gb3[4] = {}, gw4[4] = {};
-    float gb4 = 0.0f, loss = 0.0f;
-    const u64 base = ((u64)blockIdx.x * (kBlock / 64) + wv) * (u64)ta.tiles * 16;
     for (uint32_t tile = 0; tile < ta.tiles; ++tile) {
-        const u64 row0 = base + 16ull * tile;
-        __syncwarp();
-        if (lane < 16) {
-            const Sample sm = ta.batch[row0 + lane];
-            W.s[lane] = sm.s;
-            W.v[lane] = sm.v;
-            W.yt[lane] = sm.y;
-            W.wt[lane] = sm.w;
-        }
-        __syncwarp();
-        float sq[4], vq[4];
+        const Sample *sm = &T.sample[tile & 1][4 * g];
+        // the next tile's samples are under way while this one is worked on
+        const bool fetch = n == 0 && lane < 16 && tile + 1 < ta.tiles;
+        f32x4 next = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        if (fetch) next = *reinterpret_cast<const f32x4 *>(batch + 16ull * (tile + 1) + lane);
+        float pre1[2][4], pre2[2][4], pre3[2][4], h[2][4];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            sq[q] = W.s[4 * g + q];
-            vq[q] = W.v[4 * g + q];
-        }
-        // layer 1 (C layout)
-        float pre1[4][4], h1[4][4];
-#pragma unroll
-        for (int n = 0; n < 4; ++n) {
-            const int u = 16 * n + r;
+        for (int m = 0; m < 2; ++m)
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                pre1[n][q] = fmaf(M.w1[u][0], sq[q], fmaf(M.w1[u][1], vq[q], M.b1[u]));
-                h1[n][q] = mlp_act(pre1[n][q]);
+                pre1[m][q] = fmaf(w10[m], sm[q].s, fmaf(w11[m], sm[q].v, b1[m]));
+                h[m][q] = mlp_act(pre1[m][q]);
             }
-        }
-        bf16x8 a0, a1;
-        f32x4 acc[4];
-        gemm_split(transpose_split(W, h1, r, g), L.tf2, L.tl2, lane, acc);
-        float pre2[4][4], h2[4][4];
+        share(0, h);
+        __syncthreads();
+        f32x4 acc[2];
+        forward(0, acc);
 #pragma unroll
-        for (int n = 0; n < 4; ++n)
+        for (int m = 0; m < 2; ++m)
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                pre2[n][q] = acc[n][q] + M.b2[16 * n + r];
-                h2[n][q] = mlp_act(pre2[n][q]);
+                pre2[m][q] = acc[m][q] + b2[m];
+                h[m][q] = mlp_act(pre2[m][q]);
             }
-        gemm_split(transpose_split(W, h2, r, g), L.tf3, L.tl3, lane, acc);
-        float pre3[4][4], h3[4][4];
+        share(1, h);
+        __syncthreads();
+        forward(1, acc);
 #pragma unroll
-        for (int n = 0; n < 4; ++n)
+        for (int m = 0; m < 2; ++m)
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                pre3[n][q] = acc[n][q] + M.b3[16 * n + r];
-                h3[n][q] = mlp_act(pre3[n][q]);
+                pre3[m][q] = acc[m][q] + b3[m];
+                h[m][q] = mlp_act(pre3[m][q]);
+                T.h3[4 * g + q][32 * n + 16 * m + r] = h[m][q];
             }
-        float y[4];
+        __syncthreads();
+        // the output, in both waves; loss and output gradient
+        float dz[2][4];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             float sacc = 0.0f;
 #pragma unroll
-            for (int n = 0; n < 4; ++n) sacc = fmaf(M.w4[16 * n + r], h3[n][q], sacc);
-            y[q] = sacc;
-        }
-#pragma unroll
-        for (int o = 1; o < 16; o <<= 1)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) y[q] += __shfl_xor(y[q], o);
-        // loss and output gradient
-        float dy[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const float e = y[q] + M.b4 - W.yt[4 * g + q];
-            const float wq = W.wt[4 * g + q];
-            dy[q] = 2.0f * wq * e * ta.inv_batch;
-            if (r == 0) {
+            for (int k = 0; k < 4; ++k) sacc = fmaf(L.t.w4[16 * k + r], T.h3[4 * g + q][16 * k + r], sacc);
+            const float y = row_sum(sacc);
+            const float e = y + b4 - sm[q].y;
+            const float wq = sm[q].w;
+            const float dy = 2.0f * wq * e * ta.inv_batch;
+            if (n == 0 && r == 0) {
                 loss = fmaf(wq * e * e, ta.inv_batch, loss);
-                gb4 += dy[q];
-            }
-        }
-        float dz[4][4];
-#pragma unroll
-        for (int n = 0; n < 4; ++n) {
-            const float w4 = M.w4[16 * n + r];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                gw4[n] = fmaf(dy[q], h3[n][q], gw4[n]);
-                dz[n][q] = dy[q] * w4 * mlp_dact(pre3[n][q]);
-                gb3[n] += dz[n][q];
-            }
-        }
-        // dW3 += dz3^T h2 (K = the 16 samples of the tile)
-#pragma unroll
-        for (int ci = 0; ci < 4; ++ci) {
-            const s16x4 ad = pack4(dz[ci]);
-#pragma unroll
-            for (int cj = 0; cj < 4; ++cj)
-                gw3[ci * 4 + cj] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ad, pack4(h2[cj]), gw3[ci * 4 + cj], 0, 0, 0);
-        }
-        // dh2 = dz3 W3
-        transpose_to_a(W, dz, r, g, a0, a1);
-        gemm_64(a0, a1, L.wt3, lane, acc);
-#pragma unroll
-        for (int n = 0; n < 4; ++n)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                dz[n][q] = acc[n][q] * mlp_dact(pre2[n][q]);
-                gb2[n] += dz[n][q];
+                gb4 += dy;
             }
 #pragma unroll
-        for (int ci = 0; ci < 4; ++ci) {
-            const s16x4 ad = pack4(dz[ci]);
-#pragma unroll
-            for (int cj = 0; cj < 4; ++cj)
-                gw2[ci * 4 + cj] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ad, pack4(h1[cj]), gw2[ci * 4 + cj], 0, 0, 0);
+            for (int m = 0; m < 2; ++m) {
+                gw4[m] = fmaf(dy, h[m][q], gw4[m]);
+                dz[m][q] = dy * w4[m] * mlp_dact(pre3[m][q]);
+                gb3[m] += dz[m][q];
+            }
         }
-        // dh1 = dz2 W2
-        transpose_to_a(W, dz, r, g, a0, a1);
-        gemm_64(a0, a1, L.wt2, lane, acc);
+        weight_grad(0, dz, 1, gw3);
+        __syncthreads();
+        backward(0, acc);   // dh2 = dz3 W3
 #pragma unroll
-        for (int n = 0; n < 4; ++n)
+        for (int m = 0; m < 2; ++m)
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                const float d1 = acc[n][q] * mlp_dact(pre1[n][q]);
-                gw1[n][0] = fmaf(d1, sq[q], gw1[n][0]);
-                gw1[n][1] = fmaf(d1, vq[q], gw1[n][1]);
-                gb1[n] += d1;
+                dz[m][q] = acc[m][q] * mlp_dact(pre2[m][q]);
+                gb2[m] += dz[m][q];
+            }
+        if (fetch) *reinterpret_cast<f32x4 *>(&T.sample[(tile + 1) & 1][lane]) = next;
+        weight_grad(1, dz, 0, gw2);
+        __syncthreads();
+        backward(1, acc);   // dh1 = dz2 W2
+#pragma unroll
+        for (int m = 0; m < 2; ++m)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const float d1 = acc[m][q] * mlp_dact(pre1[m][q]);
+                gw10[m] = fmaf(d1, sm[q].s, gw10[m]);
+                gw11[m] = fmaf(d1, sm[q].v, gw11[m]);
+                gb1[m] += d1;
             }
     }
-    // per-column sums over the four lane groups, then the block reduction
+    // per-unit sums over the four lane groups
 #pragma unroll
-    for (int o = 16; o < 64; o <<= 1) {
+    for (int o = 16; o < 64; o <<= 1)
 #pragma unroll
-        for (int n = 0; n < 4; ++n) {
-            gw1[n][0] += __shfl_xor(gw1[n][0], o);
-            gw1[n][1] += __shfl_xor(gw1[n][1], o);
-            gb1[n] += __shfl_xor(gb1[n], o);
-            gb2[n] += __shfl_xor(gb2[n], o);
-            gb3[n] += __shfl_xor(gb3[n], o);
-            gw4[n] += __shfl_xor(gw4[n], o);
+        for (int m = 0; m < 2; ++m) {
+            gw10[m] += __shfl_xor(gw10[m], o);
+            gw11[m] += __shfl_xor(gw11[m], o);
+            gb1[m] += __shfl_xor(gb1[m], o);
+            gb2[m] += __shfl_xor(gb2[m], o);
+            gb3[m] += __shfl_xor(gb3[m], o);
+            gw4[m] += __shfl_xor(gw4[m], o);
         }
-    }
-    // The block's sum: the four waves add their partial sums in a fixed order (one
-    // wave at a time, its lanes writing distinct entries), so the float sums, and
-    // with them a training run, are the same on every run.
-    float *red = L.red;
     gb4 = wave_sum_f(gb4);
     loss = wave_sum_f(loss);
-    for (int turn = 0; turn < kBlock / 64; ++turn) {
-        __syncthreads();
-        if ((int)(threadIdx.x / 64) != turn) continue;
+    // The block's sum: every group leaves its sums in the LDS (the tiles are done with),
+    // and the threads add the four up in the order of the groups, so the float sums, and
+    // with them a training run, are the same on every run.
+    __syncthreads();
+    float *red = L.red[grp];
+#pragma unroll
+    for (int m = 0; m < 2; ++m) {
+        const int u = 32 * n + 16 * m;
         if (g == 0) {
+            red[kOffW1 + 2 * (u + r)] = gw10[m];
+            red[kOffW1 + 2 * (u + r) + 1] = gw11[m];
+            red[kOffB1 + u + r] = gb1[m];
+            red[kOffB2 + u + r] = gb2[m];
+            red[kOffB3 + u + r] = gb3[m];
+            red[kOffW4 + u + r] = gw4[m];
+        }
 #pragma unroll
-            for (int n = 0; n < 4; ++n) {
-                const int u = 16 * n + r;
-                red[kOffW1 + 2 * u] += gw1[n][0];
-                red[kOffW1 + 2 * u + 1] += gw1[n][1];
-                red[kOffB1 + u] += gb1[n];
-                red[kOffB2 + u] += gb2[n];
-                red[kOffB3 + u] += gb3[n];
-                red[kOffW4 + u] += gw4[n];
+        for (int cj = 0; cj < 4; ++cj)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int idx = (u + 4 * g + q) * kHid + 16 * cj + r;
+                red[kOffW2 + idx] = gw2[m][cj][q];
+                red[kOffW3 + idx] = gw3[m][cj][q];
             }
-        }
-        if (lane == 0) {
-            red[kOffB4] += gb4;
-            red[kMlpParams] += loss;
-        }
-#pragma unroll
-        for (int ci = 0; ci < 4; ++ci)
-#pragma unroll
-            for (int cj = 0; cj < 4; ++cj)
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int idx = (16 * ci + 4 * g + q) * kHid + 16 * cj + r;
-                    red[kOffW2 + idx] += gw2[ci * 4 + cj][q];
-                    red[kOffW3 + idx] += gw3[ci * 4 + cj][q];
-                }
+    }
+    if (n == 0 && lane == 0) {
+        red[kOffB4] = gb4;
+        red[kMlpParams] = loss;
     }
     __syncthreads();
-    float *dst = ta.partials + (u64)blockIdx.x * (kMlpParams + 1);
-    for (int i = threadIdx.x; i <= kMlpParams; i += kBlock) dst[i] = red[i];
+    float *dst = ta.partials + (u64)blockIdx.x * kRed;
+    for (int i = threadIdx.x; i < kRed; i += kTrainBlock) {
+        float sum = 0.0f;
+#pragma unroll
+        for (int k = 0; k < kTrainGroups; ++k) sum += L.red[k][i];
+        dst[i] = sum;
+    }
 }
 
 // Sum of the block gradients; then Adam (grad_out == nullptr) or a plain copy of
@@ -599,7 +594,9 @@ __global__ __launch_bounds__(kBlock) void k_mlp_reduce(ReduceArgs ra) {
     const float v = ra.beta2 * ra.v[p] + (1.0f - ra.beta2) * gsum * gsum;
     ra.m[p] = m;
     ra.v[p] = v;
-    ra.params[p] -= ra.lr * (m * ra.c1) / (sqrtf(v * ra.c2) + ra.eps);
+    const float next = ra.params[p] - ra.lr * (m * ra.c1) / (sqrtf(v * ra.c2) + ra.eps);
+    ra.params[p] = next;
+    pack_weight(reinterpret_cast<TrainWeights *>(ra.weights), p, next);
 }
 
 __global__ __launch_bounds__(kBlock) void k_mlp_pack(const float *params, MlpModel *out) {
@@ -698,7 +695,13 @@ hipError_t launch_mlp_data(const CdfTableDev &t, Sample *out, u64 n, uint64_t se
 }
 
 hipError_t launch_mlp_train(const TrainArgs &ta, int blocks, hipStream_t s) {
-    hipLaunchKernelGGL(k_mlp_train, dim3(blocks), dim3(kBlock), 0, s, ta);
+    hipLaunchKernelGGL(k_mlp_train, dim3(blocks), dim3(kTrainBlock), 0, s, ta);
+    return hipGetLastError();
+}
+
+hipError_t launch_train_pack(const float *params, void *weights, hipStream_t s) {
+    hipLaunchKernelGGL(k_train_pack, dim3((kMlpParams + kBlock - 1) / kBlock), dim3(kBlock), 0, s, params,
+                       static_cast<TrainWeights *>(weights));
     return hipGetLastError();
 }
 

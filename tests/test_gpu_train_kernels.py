@@ -33,3 +33,23 @@ def test_gradient_sum_takes_every_block(blocks):
     share = rows.size / n
     assert abs(loss - loss1 * share) <= 1e-5 * loss1 * share
     assert np.max(np.abs(grad - grad1 * share)) <= 2.0 ** -8 * np.max(np.abs(grad1)) * share
+
+
+@pytest.mark.parametrize("blocks,tiles", ((16, 1), (8, 2), (5, 3), (1, 16)))
+def test_step_does_not_depend_on_the_split(blocks, tiles):
+    """One optimizer step over the same samples (they are drawn by their number) in
+    another split over blocks and tiles: the loss agrees to the rounding of float sums
+    of 1,024 positive terms (1,024 2^-24 = 6e-5).  Adam's first step moves a parameter by
+    lr g / (|g| + 1e-8), so parameters move alike but for those whose gradient is
+    lost in that rounding or near 1e-8: one in a hundred is allowed."""
+    def step(blocks, tiles):
+        g = qed.Generator(capacity=(1, 1, 1))
+        cfg = qed.qed_train_config_default()
+        cfg.table_chi, cfg.table_x, cfg.steps, cfg.blocks, cfg.batch_tiles = 33, 512, 1, blocks, tiles
+        params, loss, _, _ = qed.qed_train_sampler(g.ctx, cfg)
+        g.close()
+        return params, loss[0], cfg.lr
+    params, loss, lr = step(blocks, tiles)
+    ref, ref_loss, _ = step(blocks * tiles, 1)
+    assert abs(loss - ref_loss) <= 6e-5 * ref_loss
+    assert np.mean(np.abs(params - ref) > 1e-3 * lr) <= 0.01
