@@ -1179,11 +1179,17 @@ qed_status qed_train_sampler(qed_ctx *c, const qed_train_config *cfg, const floa
     HIP_TRY(hipMemsetAsync(bin_err, 0, cfg->nbins * sizeof(float), c->stream));
     if (qed::launch_train_pack(params, weights, c->stream) != hipSuccess) return QED_ERR_HIP;
     const double beta1 = 0.9, beta2 = 0.999;
-    const int data_blocks = grid_for(batch, c->num_cu * 8);
+    qed::DataArgs da;
+    da.t = t;
+    da.out = data;
+    da.n = batch;
+    da.seed = cfg->seed;
+    da.step = 0;
+    da.lo10 = cfg->log10_chi_lo;
+    da.hi10 = cfg->log10_chi_hi;
+    da.blocks = grid_for(batch, c->num_cu * 8);
+    if (qed::launch_mlp_data(da, c->stream) != hipSuccess) return QED_ERR_HIP;
     for (uint32_t k = 0; k < cfg->steps; ++k) {
-        if (qed::launch_mlp_data(t, data, batch, cfg->seed, k, cfg->log10_chi_lo, cfg->log10_chi_hi, data_blocks,
-                                 c->stream) != hipSuccess)
-            return QED_ERR_HIP;
         qed::TrainArgs ta;
         ta.params = params;
         ta.weights = weights;
@@ -1208,7 +1214,9 @@ qed_status qed_train_sampler(qed_ctx *c, const qed_train_config *cfg, const floa
         ra.eps = 1e-8f;
         ra.c1 = (float)(1.0 / (1.0 - pow(beta1, k + 1.0)));
         ra.c2 = (float)(1.0 / (1.0 - pow(beta2, k + 1.0)));
-        if (qed::launch_mlp_reduce(ra, c->stream) != hipSuccess) return QED_ERR_HIP;
+        da.step = k + 1;
+        if (qed::launch_mlp_reduce(ra, k + 1 < cfg->steps ? &da : nullptr, c->stream) != hipSuccess)
+            return QED_ERR_HIP;
     }
     // validation of the packed network on the table
     if (qed::launch_mlp_pack(params, model, c->stream) != hipSuccess) return QED_ERR_HIP;
@@ -1268,7 +1276,7 @@ qed_status qed_mlp_gradient(qed_ctx *c, const float *params, const float *sample
     ra.blocks = blocks;
     ra.grad_out = grad;
     ra.loss_out = loss;
-    if (qed::launch_mlp_reduce(ra, c->stream) != hipSuccess) return QED_ERR_HIP;
+    if (qed::launch_mlp_reduce(ra, nullptr, c->stream) != hipSuccess) return QED_ERR_HIP;
     HIP_TRY(hipStreamSynchronize(c->stream));
     HIP_TRY(hipMemcpy(grad_out, grad, QED_MLP_NPARAMS * sizeof(float), hipMemcpyDeviceToHost));
     if (loss_out) HIP_TRY(hipMemcpy(loss_out, loss, sizeof(float), hipMemcpyDeviceToHost));

@@ -210,11 +210,22 @@ struct ReduceArgs {
 hipError_t launch_rate(const float *chi, float *out, u64 n, int blocks, hipStream_t s);
 hipError_t launch_pair_rate(const float *chi, float *out, u64 n, int blocks, hipStream_t s);
 hipError_t launch_cdf_table(const CdfTableDev &t, hipStream_t s);
-hipError_t launch_mlp_data(const CdfTableDev &t, Sample *out, u64 n, uint64_t seed, uint32_t step,
-                           double lo10, double hi10, int blocks, hipStream_t s);
+// The samples of one optimizer step.
+struct DataArgs {
+    CdfTableDev t;
+    Sample *out;
+    u64 n;
+    uint64_t seed;
+    uint32_t step;
+    double lo10, hi10;
+    int blocks;   // of the launch that draw samples
+};
+
+hipError_t launch_mlp_data(const DataArgs &da, hipStream_t s);
 hipError_t launch_mlp_train(const TrainArgs &ta, int blocks, hipStream_t s);
 hipError_t launch_train_pack(const float *params, void *weights, hipStream_t s);
-hipError_t launch_mlp_reduce(const ReduceArgs &ra, hipStream_t s);
+// next: samples to draw in the same launch, or null
+hipError_t launch_mlp_reduce(const ReduceArgs &ra, const DataArgs *next, hipStream_t s);
 hipError_t launch_mlp_pack(const float *params, MlpModel *out, hipStream_t s);
 hipError_t launch_mlp_validate(const MlpModel *model, const CdfTableDev &t, int nbins, int per_bin,
                                float *bin_err, hipStream_t s);
