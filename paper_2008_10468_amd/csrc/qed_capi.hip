@@ -542,7 +542,7 @@ qed_status step_impl(qed_ctx *c, qed_particles *p, const qed_field fields[3], do
         if (r == hipSuccess && emission) r = launch(c, qed::K_LEPTON, a, prec, lepton_blocks);
     }
     a.gen = 0;
-    if (r == hipSuccess) r = launch(c, qed::K_END, a, prec, 1);
+    if (r == hipSuccess && !pairs) r = launch(c, qed::K_END, a, prec, 1);
     if (r == hipSuccess && pairs) r = launch(c, qed::K_FILL, a, prec, aux_blocks);
     if (r == hipSuccess && pairs) r = launch(c, qed::K_MOVE, a, prec, aux_blocks);
     return r == hipSuccess ? QED_OK : QED_ERR_HIP;

@@ -118,7 +118,7 @@ struct StepArgs {
     const MlpModel *pair_model;  // photon path: network of the energy split (nullptr: rejection)
     uint32_t gen;          // 0: main pass; g >= 1: cascade pass g over DevState's lo..hi,
                            // each particle starting at its birth time
-    uint32_t *step_dev;    // non-null: the step number is *step_dev (k_end increments it)
+    uint32_t *step_dev;    // non-null: the step number is *step_dev (the end of the step increments it)
     u64 *gap_hist;         // non-null: event-gap histograms [2][gap_bins] (emissions, pairs)
     uint32_t gap_bins;
     CellDev cells;         // sub-steps per cell (cells.n[0] null: per particle)
