@@ -287,9 +287,9 @@ typedef struct qed_tuning {
                                       queue, and the tile pass is not launched) */
     uint32_t chunk;                /* binned scheduler: queue entries a wave claims at once
                                       (a multiple of 64, >= 64) */
-    uint32_t resolve_batch;        /* surrogate sampler: emissions a wave lets wait before it
-                                      resolves them together (1..64; results do not depend
-                                      on it) */
+    uint32_t resolve_batch;        /* candidates (Algorithm 1) or emissions (surrogate sampler)
+                                      a wave lets wait before it resolves them together
+                                      (1..64; results do not depend on it) */
     uint32_t prepass_blocks_per_cu; /* binned scheduler: grid of the pre-pass (1..1024) */
     uint32_t prepass_finish;       /* binned scheduler, 0 or 1: the pre-pass itself finishes
                                       particles whose step is a single sub-step without an

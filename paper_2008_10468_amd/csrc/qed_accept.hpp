@@ -42,21 +42,26 @@ struct AcceptBound {
     uint32_t row;
 };
 
-// kcb chi / gamma / x times the density is the acceptance probability (kcb: see PushConst).
-// The table serves chi in [2^-40, 2^12); outside it yb is infinite and every candidate
-// is evaluated (t = 0 then gives a NaN, which compares as "not rejected").
+// The bound of scale times the density; c: chi.
 template <class R>
-__device__ __forceinline__ AcceptBound<R> accept_bound(R kcb, R chi, R ig, const AcceptTable &t) {
-    const float c = (float)chi;
+__device__ __forceinline__ AcceptBound<R> scaled_bound(R scale, float c, const AcceptTable &t) {
     const float l = __builtin_amdgcn_logf(c);
     const bool in = c >= 0x1p-40f && c < (float)(1 << (AcceptTable::kL0 + AcceptTable::kRow));
     const int j = in ? min(max((int)floorf(l) - AcceptTable::kL0, 0), AcceptTable::kRow - 1) : 0;
     // b^(-1/3) = 2^(-log2(1.5 chi) / 3)
     const float bm13 = __builtin_amdgcn_exp2f(-(l + 0.58496250072f) * (1.0f / 3.0f));
     AcceptBound<R> o;
-    o.yb = in ? kcb * chi * ig * (R)(t.top[j] * bm13) : (R)__builtin_inff();
+    o.yb = in ? scale * (R)(t.top[j] * bm13) : (R)__builtin_inff();
     o.row = (uint32_t)j * AcceptTable::kBins;
     return o;
+}
+
+// kcb chi / gamma / x times the density is the acceptance probability (kcb: see PushConst).
+// The table serves chi in [2^-40, 2^12); outside it yb is infinite and every candidate
+// is evaluated (t = 0 then gives a NaN, which compares as "not rejected").
+template <class R>
+__device__ __forceinline__ AcceptBound<R> accept_bound(R kcb, R chi, R ig, const AcceptTable &t) {
+    return scaled_bound(kcb * chi * ig, (float)chi, t);
 }
 
 // Whether a candidate with word w and test value y (as large as yb counts it) may be

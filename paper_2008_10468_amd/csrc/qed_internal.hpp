@@ -101,7 +101,7 @@ struct StepArgs {
     int emission, pairs;   // which algorithms run in this step
     uint32_t light_max;    // binned scheduler: largest N handled by the light pass
     uint32_t chunk;        // binned scheduler: queue entries claimed per wave (multiple of 64)
-    uint32_t resolve_batch;  // surrogate: waiting emissions that trigger a batched resolve (1..64)
+    uint32_t resolve_batch;  // waiting candidates or emissions that trigger a batched resolve (1..64)
     uint32_t prepass_finish; // binned: the pre-pass finishes particles of one quiet sub-step
     uint32_t bins_per_octave; // binned: sub-step-count bins per octave (4..kMaxBinsPerOctave)
     uint32_t light_tile;     // binned: slots per wave tile of the light pass (64..512, a multiple of 64)
