@@ -91,37 +91,40 @@ struct __attribute__((packed, aligned(sizeof(R)))) RowPair {
     R a, b;
 };
 
-// Particles in random order put every lane of a load on a cache line of its own, and the
-// compute unit serves one line per cycle and request: with one load per corner the 48
-// loads of a particle took 177 us for 1,048,576 particles on 64^3 cells.  The two corners
-// along x are neighbours in memory and come with one load (24), except where the row
-// wraps; every axis has two lattices (on the nodes and half a cell further), computed once
-// for all components: 117 us.
-template <class R>
-__global__ __launch_bounds__(kGridBlock) void k_gather(GridDev g, GatherArgs a) {
-    const u64 n0 = *a.n;
-    const u64 n = n0 < a.cap ? n0 : a.cap;
-    for (u64 p = (u64)blockIdx.x * kGridBlock + threadIdx.x; p < n; p += (u64)gridDim.x * kGridBlock) {
-        const double x = a.x[p], y = a.y[p], z = a.z[p];
-        if (!on_grid(g, x, y, z)) {
+// The six components at one position.  The two corners along x are neighbours in memory
+// and come with one load, except where the row wraps; every axis has two lattices (on the
+// nodes and half a cell further), computed once for all components.  TOGETHER: a
+// component's four pairs in flight at once, else one after the other (the same values).
+template <class R, bool TOGETHER>
+__device__ __forceinline__ void gather_at(const GridDev &g, const GatherArgs &a, u64 p, const AxisPoint *ax,
+                                          const AxisPoint *ay, const AxisPoint *az) {
 #pragma unroll
-            for (int c = 0; c < 6; ++c) ((R *)a.out[c])[p] = (R)NAN;
-            continue;
-        }
-        const double sx = (x - g.x0) * g.idx, sy = (y - g.y0) * g.idy, sz = (z - g.z0) * g.idz;
-        const AxisPoint ax[2] = {axis_point(sx, g.nx), axis_point(sx - 0.5, g.nx)};
-        const AxisPoint ay[2] = {axis_point(sy, g.ny), axis_point(sy - 0.5, g.ny)};
-        const AxisPoint az[2] = {axis_point(sz, g.nz), axis_point(sz - 0.5, g.nz)};
+    for (int c = 0; c < 6; ++c) {
+        // Ex (1, 0, 0), Ey (0, 1, 0), Ez (0, 0, 1), Bx (0, 1, 1), By (1, 0, 1), Bz (1, 1, 0)
+        const AxisPoint &px = ax[c == 0 || c == 4 || c == 5], &py = ay[c == 1 || c == 3 || c == 5],
+                        &pz = az[c == 2 || c == 3 || c == 4];
+        const R *f = (const R *)g.f[c];
+        const bool wraps = px.hi == 0;
+        // a row's last point is read as the second of its pair (a one-point row: alone)
+        const uint32_t at = wraps && px.lo ? px.lo - 1 : px.lo;
+        R lo[4], hi[4];
+        if (TOGETHER && g.nx > 1) {
+            const R *row[4];
 #pragma unroll
-        for (int c = 0; c < 6; ++c) {
-            // Ex (1, 0, 0), Ey (0, 1, 0), Ez (0, 0, 1), Bx (0, 1, 1), By (1, 0, 1), Bz (1, 1, 0)
-            const AxisPoint &px = ax[c == 0 || c == 4 || c == 5], &py = ay[c == 1 || c == 3 || c == 5],
-                            &pz = az[c == 2 || c == 3 || c == 4];
-            const R *f = (const R *)g.f[c];
-            const bool wraps = px.lo + 1 == g.nx;
-            // a row's last point is read as the second of its pair (a one-point row: alone)
-            const uint32_t at = wraps && px.lo ? px.lo - 1 : px.lo;
-            R lo[4], hi[4];
+            for (int q = 0; q < 4; ++q) {
+                row[q] = f + (u64)((q & 2 ? pz.hi : pz.lo) * g.ny + (q & 1 ? py.hi : py.lo)) * g.nx;
+                const RowPair<R> v = *reinterpret_cast<const RowPair<R> *>(row[q] + at);
+                lo[q] = v.a;
+                hi[q] = v.b;
+            }
+            if (wraps) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    lo[q] = hi[q];
+                    hi[q] = *row[q];
+                }
+            }
+        } else {
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const u64 row = (u64)((q & 2 ? pz.hi : pz.lo) * g.ny + (q & 1 ? py.hi : py.lo)) * g.nx;
@@ -134,15 +137,58 @@ __global__ __launch_bounds__(kGridBlock) void k_gather(GridDev g, GatherArgs a) 
                     lo[q] = hi[q] = f[row];
                 }
             }
-            double v = 0.0;
+        }
+        double v = 0.0;
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const double wy = q & 1 ? py.w1 : py.w0, wz = q & 2 ? pz.w1 : pz.w0;
-                const double w0 = px.w0 * wy * wz, w1 = px.w1 * wy * wz;
-                v += w0 * (double)lo[q];
-                v += w1 * (double)hi[q];
-            }
-            ((R *)a.out[c])[p] = (R)v;
+        for (int q = 0; q < 4; ++q) {
+            const double wy = q & 1 ? py.w1 : py.w0, wz = q & 2 ? pz.w1 : pz.w0;
+            const double w0 = px.w0 * wy * wz, w1 = px.w1 * wy * wz;
+            v += w0 * (double)lo[q];
+            v += w1 * (double)hi[q];
+        }
+        ((R *)a.out[c])[p] = (R)v;
+    }
+}
+
+// One particle per lane.  Particles in random order put every lane of a load on a cache
+// line of its own, and the lines' rate bounds: fewer requests, and few of them in flight,
+// so that the waves of the chip read the same component at a time and find it in the L2.
+// In cell order the lanes share lines and the latency bounds.  A wave whose lanes change
+// their row of cells more than kGatherRows times takes the first form, where
+// kGatherPairs particles fill the chip.  us for 1,048,576 particles on 64^3 cells, float and double:
+// random order 175 / 227 with a load per corner, 108 / 141 with pairs one after the other, 136 / 241
+// together; cell order 40 / 45, 46 / 48, 37 / 39.  200,000 particles: random 47 / 59, 27 / 35,
+// 33 / 44; cell order 12 / 13, 13 / 16, 12 / 14.
+constexpr u64 kGatherPairs = 1u << 16;
+constexpr int kGatherRows = 16;
+
+template <class R>
+__global__ __launch_bounds__(kGridBlock) void k_gather(GridDev g, GatherArgs a) {
+    const u64 n0 = *a.n;
+    const u64 n = n0 < a.cap ? n0 : a.cap;
+    for (u64 p = (u64)blockIdx.x * kGridBlock + threadIdx.x; p < n; p += (u64)gridDim.x * kGridBlock) {
+        double x = a.x[p], y = a.y[p], z = a.z[p];
+        const bool on = on_grid(g, x, y, z);
+        if (!on) {
+            x = g.x0;
+            y = g.y0;
+            z = g.z0;
+        }
+        const AxisPoint ax[2] = {axis_point((x - g.x0) * g.idx, g.nx), axis_point((x - g.x0) * g.idx - 0.5, g.nx)};
+        const AxisPoint ay[2] = {axis_point((y - g.y0) * g.idy, g.ny), axis_point((y - g.y0) * g.idy - 0.5, g.ny)};
+        const AxisPoint az[2] = {axis_point((z - g.z0) * g.idz, g.nz), axis_point((z - g.z0) * g.idz - 0.5, g.nz)};
+        bool scattered = false;
+        if (n >= kGatherPairs) {
+            const uint32_t row = az[0].lo * g.ny + ay[0].lo, before = __shfl_up(row, 1);
+            scattered = __popcll(__ballot(__lane_id() == 0 || row != before)) > kGatherRows;
+        }
+        if (!on) {
+#pragma unroll
+            for (int c = 0; c < 6; ++c) ((R *)a.out[c])[p] = (R)NAN;
+        } else if (scattered) {
+            gather_at<R, false>(g, a, p, ax, ay, az);
+        } else {
+            gather_at<R, true>(g, a, p, ax, ay, az);
         }
     }
 }
