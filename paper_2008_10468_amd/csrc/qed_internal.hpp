@@ -265,13 +265,15 @@ constexpr uint32_t kBinLdsTiles = 4096;         // up to this many tiles counted
 constexpr uint32_t kDepMaxTiles = 1u << 18;     // beyond: the wave-run kernel
 constexpr uint32_t kDepRows = 256;              // blocks of the row-wise tile count (k_dep_rows)
 constexpr uint32_t kDepRowTiles = 16384;        // up to this many tiles counted row-wise
-// Whether a deposit counts its tiles row by row.  The other way, one atomic add on the tile's
-// counter for every tile that a block of 2,048 particles touches (for every particle beyond
-// kBinLdsTiles), serves about 8 adds per ns: 249 us for 2,000,003 particles in random order on
-// 4,992 tiles, 22 row by row.  That costs 16 bytes of traffic per row and tile and two more
-// launches, so it is taken where random order would need more than 2^18 adds (33 us).
+// Whether a deposit counts its tiles row by row.  Beyond kBinLdsTiles tiles the other way takes
+// one atomic add on the tile's counter for every particle, some 8 per ns: 249 us for 2,000,003
+// particles in random order on 4,992 tiles, 22 row by row (15,625 tiles: the whole deposit 391
+// and 279 us, in cell order 369 and 247; 600,000 particles 177 and 150).  Up to kBinLdsTiles the
+// blocks count in LDS, which is as fast (512 and 4,096 tiles: 207 to 163 us either way, cell
+// order 3-4% faster so), and for few particles the two more launches and the 16 bytes of
+// traffic per row and tile do not pay.
 inline bool dep_by_rows(u64 cap, u64 ntiles) {
-    return ntiles <= kDepRowTiles && (ntiles < 2048 ? ntiles : 2048) * (cap / 2048) > (1u << 18);
+    return ntiles > kBinLdsTiles && ntiles <= kDepRowTiles && cap > (1u << 18);
 }
 // parts a deposit of cap slots over ntiles tiles can need
 inline u64 dep_max_parts(u64 cap, u64 ntiles) { return ntiles + (cap + kDepPart - 1) / kDepPart; }
