@@ -150,16 +150,43 @@ __device__ __forceinline__ void gather_at(const GridDev &g, const GatherArgs &a,
     }
 }
 
+// Few particles, a wave or less per SIMD: only latency counts, and every corner's load is
+// independent of the others, without a branch (the same values).  Taken below kGatherPairs
+// slots: 20,000 particles in cell order on 64^3 cells 8.2 us, 10.0 with the pairs of
+// k_gather; 70,000 in random order 24 (double 31) and 19 (24).
+constexpr u64 kGatherPairs = 1u << 16;
+
+template <class R>
+__global__ __launch_bounds__(kGridBlock) void k_gather_few(GridDev g, GatherArgs a) {
+    const u64 n0 = *a.n;
+    const u64 n = n0 < a.cap ? n0 : a.cap;
+    for (u64 p = (u64)blockIdx.x * kGridBlock + threadIdx.x; p < n; p += (u64)gridDim.x * kGridBlock) {
+        const double x = a.x[p], y = a.y[p], z = a.z[p];
+        if (!on_grid(g, x, y, z)) {
+#pragma unroll
+            for (int c = 0; c < 6; ++c) ((R *)a.out[c])[p] = (R)NAN;
+            continue;
+        }
+#pragma unroll
+        for (int c = 0; c < 6; ++c) {
+            const Corners cr = corners(g, x, y, z, kStagger[c][0], kStagger[c][1], kStagger[c][2]);
+            const R *f = (const R *)g.f[c];
+            double v = 0.0;
+#pragma unroll
+            for (int q = 0; q < 8; ++q) v += cr.w[q] * (double)f[cr.idx[q]];
+            ((R *)a.out[c])[p] = (R)v;
+        }
+    }
+}
+
 // One particle per lane.  Particles in random order put every lane of a load on a cache
 // line of its own, and the lines' rate bounds: fewer requests, and few of them in flight,
 // so that the waves of the chip read the same component at a time and find it in the L2.
 // In cell order the lanes share lines and the latency bounds.  A wave whose lanes change
-// their row of cells more than kGatherRows times takes the first form, where
-// kGatherPairs particles fill the chip.  us for 1,048,576 particles on 64^3 cells, float and double:
+// their row of cells more than kGatherRows times takes the first form.  us for 1,048,576 particles on 64^3 cells, float and double:
 // random order 175 / 227 with a load per corner, 108 / 141 with pairs one after the other, 136 / 241
 // together; cell order 40 / 45, 46 / 48, 37 / 39.  200,000 particles: random 47 / 59, 27 / 35,
 // 33 / 44; cell order 12 / 13, 13 / 16, 12 / 14.
-constexpr u64 kGatherPairs = 1u << 16;
 constexpr int kGatherRows = 16;
 
 template <class R>
@@ -177,11 +204,8 @@ __global__ __launch_bounds__(kGridBlock) void k_gather(GridDev g, GatherArgs a) 
         const AxisPoint ax[2] = {axis_point((x - g.x0) * g.idx, g.nx), axis_point((x - g.x0) * g.idx - 0.5, g.nx)};
         const AxisPoint ay[2] = {axis_point((y - g.y0) * g.idy, g.ny), axis_point((y - g.y0) * g.idy - 0.5, g.ny)};
         const AxisPoint az[2] = {axis_point((z - g.z0) * g.idz, g.nz), axis_point((z - g.z0) * g.idz - 0.5, g.nz)};
-        bool scattered = false;
-        if (n >= kGatherPairs) {
-            const uint32_t row = az[0].lo * g.ny + ay[0].lo, before = __shfl_up(row, 1);
-            scattered = __popcll(__ballot(__lane_id() == 0 || row != before)) > kGatherRows;
-        }
+        const uint32_t row = az[0].lo * g.ny + ay[0].lo, before = __shfl_up(row, 1);
+        const bool scattered = __popcll(__ballot(__lane_id() == 0 || row != before)) > kGatherRows;
         if (!on) {
 #pragma unroll
             for (int c = 0; c < 6; ++c) ((R *)a.out[c])[p] = (R)NAN;
@@ -740,8 +764,13 @@ __global__ __launch_bounds__(kGridBlock) void k_dep_reduce(GridDev g, DepSortArg
 }  // namespace
 
 hipError_t launch_gather(const GridDev &g, const GatherArgs &a, int dtype, int blocks, hipStream_t s) {
-    if (dtype == 0)
+    const bool few = a.cap < kGatherPairs;
+    if (dtype == 0 && few)
+        hipLaunchKernelGGL(k_gather_few<float>, dim3(blocks), dim3(kGridBlock), 0, s, g, a);
+    else if (dtype == 0)
         hipLaunchKernelGGL(k_gather<float>, dim3(blocks), dim3(kGridBlock), 0, s, g, a);
+    else if (few)
+        hipLaunchKernelGGL(k_gather_few<double>, dim3(blocks), dim3(kGridBlock), 0, s, g, a);
     else
         hipLaunchKernelGGL(k_gather<double>, dim3(blocks), dim3(kGridBlock), 0, s, g, a);
     return hipGetLastError();

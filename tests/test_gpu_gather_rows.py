@@ -1,5 +1,5 @@
-"""The gather's two forms, chosen by the number of particles and by how often a wave's lanes
-change their row of cells: the same bits in any order, and the oracle's values."""
+"""The gather's forms, chosen by the capacity and by how often a wave's lanes change their row
+of cells: the same bits in any of them and in any order, and the oracle's values."""
 import numpy as np
 import pytest
 
@@ -19,8 +19,8 @@ def _gather(gen, s, p, n):
     return np.stack([t.double().cpu().numpy() for t in out])
 
 
-# one below, at and above the count from which scattered waves read pair by pair; rows of
-# one point (no pairs), two (every pair ends a row), an odd number
+# one below, at and above the capacity from which pairs are read; rows of one point (no
+# pairs), two (every pair ends a row), an odd number
 @pytest.mark.parametrize("n", (65535, 65536, 65600))
 @pytest.mark.parametrize("nx", (1, 2, 17))
 @pytest.mark.parametrize("prec_name", ["F64", "MIXED"])
@@ -36,6 +36,9 @@ def test_any_order_gives_the_same_bits(n, nx, prec_name):
     cell = [np.floor((np.where(np.isfinite(p[k]), p[k], 0.0) - g[k + "0"]) / g["d" + k]) % g["n" + k] for k in "xyz"]
     order = np.lexsort(cell)
     b = _gather(gen, s, {k: v[order] for k, v in p.items()}, n)
+    gen.close()
+    gen = qed.Generator(precision=getattr(qed, "QED_PREC_" + prec_name), capacity=(2 * n, 16, 16))
+    assert np.array_equal(_gather(gen, s, p, 2 * n)[:, :n], a, equal_nan=True)   # above the line for every n
     gen.close()
     assert np.array_equal(a[:, order], b, equal_nan=True)
     on = np.isfinite(p["x"])
