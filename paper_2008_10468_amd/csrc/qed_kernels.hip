@@ -1485,7 +1485,8 @@ constexpr uint32_t kLeptonQueue = 128;   // at most 63 + 31 queued
 template <class R, bool SURR>
 __global__ __launch_bounds__(kBlock, SURR ? 2 : sizeof(R) == 4 ? 4 : 3) void k_lepton(StepArgs a) {
     __shared__ LeptonLds<R, SURR> L;
-    __shared__ uint32_t slot_sh[SURR ? kBlock / 64 : 1][kLeptonQueue], n_sh[SURR ? kBlock / 64 : 1][kLeptonQueue];
+    __shared__ u64 slot_sh[SURR ? kBlock / 64 : 1][kLeptonQueue];
+    __shared__ uint32_t n_sh[SURR ? kBlock / 64 : 1][kLeptonQueue];
     const int s = blockIdx.y;
     const u64 lo = a.st->lo[s], hi = a.st->hi[s];
     if (lo + (u64)blockIdx.x * kBlock >= hi) return;   // no particle for this block: nothing to stage
@@ -1496,7 +1497,8 @@ __global__ __launch_bounds__(kBlock, SURR ? 2 : sizeof(R) == 4 ? 4 : 3) void k_l
     const u64 G = first_lane((u64)gridDim.x * kBlock);
     u64 i0 = first_lane(lo + (u64)blockIdx.x * kBlock + (threadIdx.x & ~63u));
     if constexpr (SURR) {
-        uint32_t *qslot = slot_sh[wv], *qn = n_sh[wv];   // slot - lo, sub-steps
+        u64 *qslot = slot_sh[wv];   // whole slots: this scheduler has no limit on their number
+        uint32_t *qn = n_sh[wv];    // sub-steps
         uint32_t queued = 0;   // wave-uniform
         const uint32_t fill = hi - lo > G ? 32u : 0u;    // a wave of one 64 runs them at once
         for (;; i0 += G) {
@@ -1515,7 +1517,7 @@ __global__ __launch_bounds__(kBlock, SURR ? 2 : sizeof(R) == 4 ? 4 : 3) void k_l
             if (!more || (uint32_t)__popcll(m) < fill) {
                 if (N) {
                     const uint32_t q = queued + (uint32_t)__popcll(m & lanemask_lt());
-                    qslot[q] = (uint32_t)(i - lo);
+                    qslot[q] = i;
                     qn[q] = N;
                 }
                 queued += (uint32_t)__popcll(m);
@@ -1526,7 +1528,7 @@ __global__ __launch_bounds__(kBlock, SURR ? 2 : sizeof(R) == 4 ? 4 : 3) void k_l
                 if (run == 0) break;
                 queued -= run;
                 const bool has = lane < run;
-                i = lo + (has ? qslot[queued + lane] : 0u);
+                i = has ? qslot[queued + lane] : lo;
                 N = has ? qn[queued + lane] : 0u;
                 __syncwarp();
                 p = has ? load_lepton<R>(a, s, i) : Lepton<R>{0, 0, 0, 0, 0, 0, 0, 0, 0};
