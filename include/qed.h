@@ -290,7 +290,9 @@ typedef struct qed_tuning {
     uint32_t resolve_batch;        /* candidates (Algorithm 1) or emissions (surrogate sampler)
                                       a wave lets wait before it resolves them together
                                       (1..64; results do not depend on it) */
-    uint32_t prepass_blocks_per_cu; /* binned scheduler: grid of the pre-pass (1..1024) */
+    uint32_t prepass_blocks_per_cu; /* binned scheduler: grid of the pre-pass (1..1024; the
+                                      default is what the chip holds at once, which depends
+                                      on the context's sampler) */
     uint32_t prepass_finish;       /* binned scheduler, 0 or 1: the pre-pass itself finishes
                                       particles whose step is a single sub-step without an
                                       event, instead of the light pass reading them again

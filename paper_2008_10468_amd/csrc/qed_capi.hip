@@ -521,13 +521,8 @@ qed_status step_impl(qed_ctx *c, qed_particles *p, const qed_field fields[3], do
     if (r == hipSuccess && emission && !binned)
         r = launch(c, tiled ? qed::K_TILED : qed::K_LEPTON, a, prec, lepton_blocks);
     if (binned) {
-        // a grid between one and two times what the chip holds would leave the blocks of
-        // its second round alone on it (16.8M electrons at 7 resident blocks per CU: a
-        // grid of 8 took 473 us, one of 7 403)
-        uint32_t pb = c->tune.prepass_blocks_per_cu;
-        const uint32_t held = (uint32_t)qed::kPrepassBlocks[surrogate ? 1 : 0];
-        if (prec == 1 && pb > held && pb < 2 * held) pb = held;
-        if (r == hipSuccess) r = launch(c, qed::K_PREPASS, a, prec, grid_for(lep_cap, c->num_cu * (int)pb));
+        if (r == hipSuccess)
+            r = launch(c, qed::K_PREPASS, a, prec, grid_for(lep_cap, c->num_cu * (int)c->tune.prepass_blocks_per_cu));
         if (r == hipSuccess) r = launch(c, qed::K_SCAN, a, prec, 1);
         if (r == hipSuccess)
             r = launch(c, qed::K_SCATTER, a, prec, grid_for(lep_cap, c->num_cu * (int)c->tune.scatter_blocks_per_cu));
@@ -660,7 +655,11 @@ qed_status qed_init(qed_ctx **out, const qed_config *cfg) {
     c->tune.chunk = 256;
     c->tune.resolve_batch = 16;
     c->tune.prepass_finish = 1;
-    c->tune.prepass_blocks_per_cu = 8;
+    // what the chip holds at once: a grid between that and twice as much leaves the blocks of its
+    // second round alone on it (us for 16.8M electrons of the hot spot, blocks per CU:
+    // optical depth 4: 422, 6: 423, 7: 531, 8: 483, 12: 437; Algorithm 1 4: 412, 6: 395, 8: 399,
+    // 10: 461, 12: 427, 16: 411)
+    c->tune.prepass_blocks_per_cu = (uint32_t)qed::kPrepassBlocks[cfg->sampler == QED_SAMPLER_SURROGATE ? 1 : 0];
     c->tune.scatter_blocks_per_cu = 2;
     c->tune.bins_per_octave = 16;
     c->tune.light_tile = 512;
