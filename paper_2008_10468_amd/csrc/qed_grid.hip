@@ -91,11 +91,17 @@ struct __attribute__((packed, aligned(sizeof(R)))) RowPair {
     R a, b;
 };
 
-// The six components at one position.  The two corners along x are neighbours in memory
-// and come with one load, except where the row wraps; every axis has two lattices (on the
-// nodes and half a cell further), computed once for all components.  TOGETHER: a
-// component's four pairs in flight at once, else one after the other (the same values).
-template <class R, bool TOGETHER>
+// How a lane reads the eight corners of a component (the same values in any of them).
+enum GatherForm {
+    kCorners,    // a load per corner, all components' in flight
+    kPairs,      // the two corners along x with one load, four pairs in flight
+    kPairByPair  // the pairs one after the other
+};
+
+// The six components at one position.  The two corners along x are neighbours in memory,
+// except where the row wraps; every axis has two lattices (on the nodes and half a cell
+// further), computed once for all components.
+template <class R, GatherForm FORM>
 __device__ __forceinline__ void gather_at(const GridDev &g, const GatherArgs &a, u64 p, const AxisPoint *ax,
                                           const AxisPoint *ay, const AxisPoint *az) {
 #pragma unroll
@@ -108,7 +114,14 @@ __device__ __forceinline__ void gather_at(const GridDev &g, const GatherArgs &a,
         // a row's last point is read as the second of its pair (a one-point row: alone)
         const uint32_t at = wraps && px.lo ? px.lo - 1 : px.lo;
         R lo[4], hi[4];
-        if (TOGETHER && g.nx > 1) {
+        if constexpr (FORM == kCorners) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const R *row = f + (u64)((q & 2 ? pz.hi : pz.lo) * g.ny + (q & 1 ? py.hi : py.lo)) * g.nx;
+                lo[q] = row[px.lo];
+                hi[q] = row[px.hi];
+            }
+        } else if (FORM == kPairs && g.nx > 1) {
             const R *row[4];
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
@@ -150,43 +163,22 @@ __device__ __forceinline__ void gather_at(const GridDev &g, const GatherArgs &a,
     }
 }
 
-// Few particles, a wave or less per SIMD: only latency counts, and every corner's load is
-// independent of the others, without a branch (the same values).  Taken below kGatherPairs
-// slots: 20,000 particles in cell order on 64^3 cells 8.2 us, 10.0 with the pairs of
-// k_gather; 70,000 in random order 24 (double 31) and 19 (24).
-constexpr u64 kGatherPairs = 1u << 16;
-
-template <class R>
-__global__ __launch_bounds__(kGridBlock) void k_gather_few(GridDev g, GatherArgs a) {
-    const u64 n0 = *a.n;
-    const u64 n = n0 < a.cap ? n0 : a.cap;
-    for (u64 p = (u64)blockIdx.x * kGridBlock + threadIdx.x; p < n; p += (u64)gridDim.x * kGridBlock) {
-        const double x = a.x[p], y = a.y[p], z = a.z[p];
-        if (!on_grid(g, x, y, z)) {
-#pragma unroll
-            for (int c = 0; c < 6; ++c) ((R *)a.out[c])[p] = (R)NAN;
-            continue;
-        }
-#pragma unroll
-        for (int c = 0; c < 6; ++c) {
-            const Corners cr = corners(g, x, y, z, kStagger[c][0], kStagger[c][1], kStagger[c][2]);
-            const R *f = (const R *)g.f[c];
-            double v = 0.0;
-#pragma unroll
-            for (int q = 0; q < 8; ++q) v += cr.w[q] * (double)f[cr.idx[q]];
-            ((R *)a.out[c])[p] = (R)v;
-        }
-    }
-}
-
 // One particle per lane.  Particles in random order put every lane of a load on a cache
 // line of its own, and the lines' rate bounds: fewer requests, and few of them in flight,
-// so that the waves of the chip read the same component at a time and find it in the L2.
-// In cell order the lanes share lines and the latency bounds.  A wave whose lanes change
-// their row of cells more than kGatherRows times takes the first form.  us for 1,048,576 particles on 64^3 cells, float and double:
-// random order 175 / 227 with a load per corner, 108 / 141 with pairs one after the other, 136 / 241
-// together; cell order 40 / 45, 46 / 48, 37 / 39.  200,000 particles: random 47 / 59, 27 / 35,
-// 33 / 44; cell order 12 / 13, 13 / 16, 12 / 14.
+// so that the waves of the chip read the same component at a time and find it in the L2:
+// a wave whose lanes change their row of cells more than kGatherRows times reads pair by
+// pair.  In cell order the lanes share lines and the latency bounds: every corner's load
+// independent of the others, without a branch, until at kGatherTogether particles the chip
+// holds no more waves and the number of loads counts.  Below kGatherPairs particles there
+// is a wave or less per SIMD and only the latency counts, in any order.  The counts are
+// of the live particles, whatever the capacity.  us on 64^3 cells, float and double, in the
+// forms that a wave may take (corners; pair by pair; pairs):
+//   random order, 65,000: 14 / 17; -; 15 / 17   200,000: 46 / 58; 25 / 33; 33 / 44
+//                                             1,048,576: 172 / 231; 110 / 155; 136 / 241
+//   cell order, 20,000: 5.4 / 7.7; -; 7.1 / 12.5   262,000: 11.2 / 12.6; -; 10.5 / 13.1
+//                 400,000: 16.0 / 19.8; -; 17.8 / 20.9   1,048,576: 37.6 / 43.2; 46 / 48; 35.5 / 39.2
+constexpr u64 kGatherPairs = 1u << 16;
+constexpr u64 kGatherTogether = 1u << 19;
 constexpr int kGatherRows = 16;
 
 template <class R>
@@ -205,14 +197,17 @@ __global__ __launch_bounds__(kGridBlock) void k_gather(GridDev g, GatherArgs a) 
         const AxisPoint ay[2] = {axis_point((y - g.y0) * g.idy, g.ny), axis_point((y - g.y0) * g.idy - 0.5, g.ny)};
         const AxisPoint az[2] = {axis_point((z - g.z0) * g.idz, g.nz), axis_point((z - g.z0) * g.idz - 0.5, g.nz)};
         const uint32_t row = az[0].lo * g.ny + ay[0].lo, before = __shfl_up(row, 1);
-        const bool scattered = __popcll(__ballot(__lane_id() == 0 || row != before)) > kGatherRows;
+        const bool scattered =
+            n >= kGatherPairs && __popcll(__ballot(__lane_id() == 0 || row != before)) > kGatherRows;
         if (!on) {
 #pragma unroll
             for (int c = 0; c < 6; ++c) ((R *)a.out[c])[p] = (R)NAN;
         } else if (scattered) {
-            gather_at<R, false>(g, a, p, ax, ay, az);
+            gather_at<R, kPairByPair>(g, a, p, ax, ay, az);
+        } else if (n < kGatherTogether) {
+            gather_at<R, kCorners>(g, a, p, ax, ay, az);
         } else {
-            gather_at<R, true>(g, a, p, ax, ay, az);
+            gather_at<R, kPairs>(g, a, p, ax, ay, az);
         }
     }
 }
@@ -764,13 +759,8 @@ __global__ __launch_bounds__(kGridBlock) void k_dep_reduce(GridDev g, DepSortArg
 }  // namespace
 
 hipError_t launch_gather(const GridDev &g, const GatherArgs &a, int dtype, int blocks, hipStream_t s) {
-    const bool few = a.cap < kGatherPairs;
-    if (dtype == 0 && few)
-        hipLaunchKernelGGL(k_gather_few<float>, dim3(blocks), dim3(kGridBlock), 0, s, g, a);
-    else if (dtype == 0)
+    if (dtype == 0)
         hipLaunchKernelGGL(k_gather<float>, dim3(blocks), dim3(kGridBlock), 0, s, g, a);
-    else if (few)
-        hipLaunchKernelGGL(k_gather_few<double>, dim3(blocks), dim3(kGridBlock), 0, s, g, a);
     else
         hipLaunchKernelGGL(k_gather<double>, dim3(blocks), dim3(kGridBlock), 0, s, g, a);
     return hipGetLastError();
