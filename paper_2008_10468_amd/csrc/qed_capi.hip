@@ -236,9 +236,7 @@ qed_status ensure_cell_slots(qed_ctx *c, int s, u64 cap) {
 // graph, or out of memory: the caller then adds per wave).
 bool ensure_deposit_scratch(qed_ctx *c, u64 cap, u64 tiles) {
     const u64 parts = qed::dep_max_parts(cap, tiles);
-    const u64 row_tiles = qed::dep_by_rows(cap, tiles) ? tiles : 0;
-    if (cap <= c->dep_cap && tiles <= c->dep_tiles && parts <= c->dep_parts && row_tiles <= c->dep_row_tiles)
-        return true;
+    if (cap <= c->dep_cap && tiles <= c->dep_tiles && parts <= c->dep_parts) return true;
     if (c->capturing) return false;
     if (hipStreamSynchronize(c->stream) != hipSuccess) return false;
     bool ok = true;
@@ -269,14 +267,30 @@ bool ensure_deposit_scratch(qed_ctx *c, u64 cap, u64 tiles) {
              hipMalloc(&c->dep_stage, parts * qed::kDepStage * sizeof(double)) == hipSuccess;
         if (ok) c->dep_parts = parts;
     }
-    if (ok && row_tiles > c->dep_row_tiles) {
-        retire(c, c->dep_rows);
-        c->dep_row_tiles = 0;
-        ok = hipMalloc(&c->dep_rows, qed::kDepRows * row_tiles * sizeof(uint32_t)) == hipSuccess;
-        if (ok) c->dep_row_tiles = row_tiles;
-    }
     if (!ok) (void)hipGetLastError();   // an allocation failure is not kept as the stream's error
     return ok;
+}
+
+// The counts of a row-wise deposit, or null: not one by that rule, or they cannot be had
+// now (the stream is being captured, by the library or its caller, or out of memory);
+// the tiles are then counted without them, on the scratch that is there.
+uint32_t *deposit_rows(qed_ctx *c, u64 cap, u64 tiles) {
+    if (!qed::dep_by_rows(cap, tiles)) return nullptr;
+    if (tiles <= c->dep_row_tiles) return c->dep_rows;
+    hipStreamCaptureStatus cap_status;
+    if (c->capturing || hipStreamIsCapturing(c->stream, &cap_status) != hipSuccess ||
+        cap_status != hipStreamCaptureStatusNone || hipStreamSynchronize(c->stream) != hipSuccess) {
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    retire(c, c->dep_rows);
+    c->dep_row_tiles = 0;
+    if (hipMalloc(&c->dep_rows, qed::kDepRows * tiles * sizeof(uint32_t)) != hipSuccess) {
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    c->dep_row_tiles = tiles;
+    return c->dep_rows;
 }
 
 bool tuning_ok(const qed_tuning &t) {
@@ -828,7 +842,7 @@ qed_status qed_deposit(qed_ctx *c, const qed_grid *grid, const qed_species *sp, 
         d.pos = c->dep_pos;
         d.rec = c->dep_rec;
         d.stage = c->dep_stage;
-        d.rows = qed::dep_by_rows(sp->capacity, ntiles) ? c->dep_rows : nullptr;
+        d.rows = deposit_rows(c, sp->capacity, ntiles);
         if (qed::launch_deposit_sorted(g, d, dtype, grid_for(sp->capacity, c->num_cu * 8), c->stream) != hipSuccess)
             return QED_ERR_HIP;
         return QED_OK;
