@@ -65,7 +65,8 @@ __device__ __forceinline__ AcceptBound<R> accept_bound(R kcb, R chi, R ig, const
 }
 
 // Whether a candidate with word w and test value y (as large as yb counts it) may be
-// accepted: false is the rejection eq. (1) gives.
+// accepted: false is the rejection eq. (1) gives.  With y the largest probability so far:
+// whether the candidate's may be larger.
 template <class R>
 __device__ __forceinline__ bool accept_may(R y, uint32_t w, const AcceptBound<R> &o, const AcceptTable &t) {
     const uint8_t *b = reinterpret_cast<const uint8_t *>(&t.t[0][0]);

@@ -127,15 +127,27 @@ struct Tally {
     R max_p = 0;
 };
 
-// A lepton pass's tally.  Algorithm 1 rejects most candidates without evaluating their
-// probability, but not those whose bound lies above the largest one so far, so max_p is
-// exact; it starts at what earlier passes have found, so that few are evaluated for it alone
-// (hot spot of 16.8M electrons 1.759 to 1.768 ms a step, laser field 1.284 to 1.287 for eight).
-template <class R, bool SURR>
-__device__ __forceinline__ Tally<R> lepton_tally(const DevState *st) {
-    Tally<R> t;
-    if constexpr (!SURR) t.max_p = (R)__longlong_as_double((long long)st->max_p_bits);
-    return t;
+// The largest acceptance probability so far, in units of 1 / Draw::kYScale.  Algorithm 1
+// rejects most candidates without evaluating their probability, but not those whose bound
+// lies above this one, so max_p is exact; it starts at what earlier passes have found, and
+// a block shares it, so that few are evaluated for it alone (us a pass without and with the exact
+// value: hot spot of 16.8M electrons 1756 and 1758, shower 1265 and 1271, 16,384 ring electrons
+// in FP64 149 and 151.5; held by every lane for itself, the hot spot took 1768).
+template <class R>
+struct MaxSeen {
+    using Bits = typename std::conditional<sizeof(R) == 4, uint32_t, unsigned long long>::type;
+    Bits bits;   // of a non-negative R: ordered as it is
+    __device__ __forceinline__ R get() const { return __builtin_bit_cast(R, *(const volatile Bits *)&bits); }
+    // the larger one of p and the block's, which p joins
+    __device__ __forceinline__ R raise(R p) {
+        return fmax(p, __builtin_bit_cast(R, atomicMax(&bits, __builtin_bit_cast(Bits, p))));
+    }
+};
+
+// max_p of the earlier passes.
+template <class R>
+__device__ __forceinline__ R max_p_before(const DevState *st) {
+    return (R)__longlong_as_double((long long)st->max_p_bits);
 }
 
 // Sum over the wave, skipped (no cross-lane traffic) when the counter is zero in
@@ -712,7 +724,7 @@ __device__ __forceinline__ Rot<R> rot_chi(const Lepton<R> &p, const PushConst<R>
 // candidate evaluated, 1,400 with the bound and the waiting lanes.
 template <class R, int FK>
 __device__ __forceinline__ void lepton_loop(const StepArgs &a, int s, u64 i, uint32_t N, Lepton<R> p,
-                                            const SynTable<R> &tab, const AcceptTable &at, OriginHold<R> &oh,
+                                            const SynTable<R> &tab, const AcceptTable &at, MaxSeen<R> &ms, OriginHold<R> &oh,
                                             ChildPool<R> &cb, Tally<R> &tl, double t0) {
     constexpr bool kPairs = sizeof(R) == 4;   // two sub-steps per Philox block
     const SpeciesDev &sp = a.sp[s];
@@ -727,7 +739,7 @@ __device__ __forceinline__ void lepton_loop(const StepArgs &a, int s, u64 i, uin
     const uint32_t step = step_of(a);
     const int batch = (int)a.resolve_batch;
     const R kyb = c.kcb * Draw<R>::kYScale;
-    R seen = tl.max_p * Draw<R>::kYScale;   // the largest probability so far, as test() counts it
+    R seen = ms.get();
     R ux = p.ux, uy = p.uy, uz = p.uz;
     R dx = 0, dy = 0, dz = 0;
     uint32_t nev = 0;
@@ -776,7 +788,7 @@ __device__ __forceinline__ void lepton_loop(const StepArgs &a, int s, u64 i, uin
             R x, y;
             draw.pair(k - 1u, x, y);
             const R pm = accept_prob(c.kcb, o.chi, o.ig, x, tab, x3, omx3);
-            seen = fmax(seen, pm * Draw<R>::kYScale);
+            if (pm * Draw<R>::kYScale > seen) seen = ms.raise(pm * Draw<R>::kYScale);
             tl.clips += pm > R(1);
             acc = y < pm;
             lim = N;
@@ -803,7 +815,6 @@ __device__ __forceinline__ void lepton_loop(const StepArgs &a, int s, u64 i, uin
             if (pend && (k & 1u) != 0u && k < N) advance(1);
         }
     }
-    tl.max_p = seen / Draw<R>::kYScale;
     const Origin<R> org = oh.get(held);
     ((R *)sp.ux)[i] = ux;
     ((R *)sp.uy)[i] = uy;
@@ -818,16 +829,16 @@ __device__ __forceinline__ void lepton_loop(const StepArgs &a, int s, u64 i, uin
 
 template <class R>
 __device__ __forceinline__ void lepton_run(const StepArgs &a, int s, u64 i, uint32_t N, Lepton<R> p,
-                                           const SynTable<R> &tab, const AcceptTable &at, OriginHold<R> &oh,
+                                           const SynTable<R> &tab, const AcceptTable &at, MaxSeen<R> &ms, OriginHold<R> &oh,
                                            ChildPool<R> &cb, Tally<R> &tl, double t0) {
     const bool noB = p.bx == R(0) && p.by == R(0) && p.bz == R(0);
     const bool noE = p.ex == R(0) && p.ey == R(0) && p.ez == R(0);
     if (noB)
-        lepton_loop<R, 1>(a, s, i, N, p, tab, at, oh, cb, tl, t0);
+        lepton_loop<R, 1>(a, s, i, N, p, tab, at, ms, oh, cb, tl, t0);
     else if (noE)
-        lepton_loop<R, 2>(a, s, i, N, p, tab, at, oh, cb, tl, t0);
+        lepton_loop<R, 2>(a, s, i, N, p, tab, at, ms, oh, cb, tl, t0);
     else
-        lepton_loop<R, 0>(a, s, i, N, p, tab, at, oh, cb, tl, t0);
+        lepton_loop<R, 0>(a, s, i, N, p, tab, at, ms, oh, cb, tl, t0);
 }
 
 // ---------------------------------------------------------------------------
@@ -1110,7 +1121,7 @@ struct LeptonRunner<R, false> {
     template <bool DUAL = false, class L>
     __device__ static void run(const StepArgs &a, int s, u64 i, uint32_t N, const Lepton<R> &p, L &lds,
                                ChildPool<R> &cb, Tally<R> &t, double t0 = 0.0) {
-        if (N) lepton_run<R>(a, s, i, N, p, lds.tab, lds.acc, lds.org, cb, t, t0);
+        if (N) lepton_run<R>(a, s, i, N, p, lds.tab, lds.acc, lds.seen, lds.org, cb, t, t0);
     }
 };
 
@@ -1316,6 +1327,7 @@ template <class R, bool SURR>
 struct LeptonLds {
     SynTable<R> tab;
     AcceptTable acc;
+    MaxSeen<R> seen;
     OriginHold<R> org;
     ChildPool<R> cb;
 };
@@ -1335,6 +1347,8 @@ __device__ __forceinline__ ChildPool<R> &lepton_lds_init(const StepArgs &a, Lept
     }
     accept_stage(L.acc);
     syn_stage(L.tab);
+    if (threadIdx.x == 0)
+        L.seen.bits = __builtin_bit_cast(typename MaxSeen<R>::Bits, max_p_before<R>(a.st) * Draw<R>::kYScale);
     __syncthreads();
     return L.cb;
 }
@@ -1510,7 +1524,7 @@ __global__ __launch_bounds__(kBlock, SURR ? 2 : sizeof(R) == 4 ? 4 : 3) void k_l
     auto &cb = lepton_lds_init(a, L);
     const uint32_t lane = __lane_id();
     const uint32_t wv = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
-    Tally<R> t = lepton_tally<R, SURR>(a.st);
+    Tally<R> t;
     const u64 G = first_lane((u64)gridDim.x * kBlock);
     u64 i0 = first_lane(lo + (u64)blockIdx.x * kBlock + (threadIdx.x & ~63u));
     if constexpr (SURR) {
@@ -1564,7 +1578,8 @@ __global__ __launch_bounds__(kBlock, SURR ? 2 : sizeof(R) == 4 ? 4 : 3) void k_l
             LeptonRunner<R, SURR>::run(a, s, i, N, p, L, cb, t, t0);
         }
     }
-    flush_children_block(L.cb, a.sp[2], a.seed, step_of(a));
+    flush_children_block(L.cb, a.sp[2], a.seed, step_of(a));   // begins with a barrier
+    if constexpr (!SURR) t.max_p = L.seen.get() / Draw<R>::kYScale;
     flush_tally(t, a.st, s);
 }
 
@@ -1591,7 +1606,8 @@ __global__ __launch_bounds__(kBlock, sizeof(R) == 4 ? kPrepassBlocks[SURR] : 4) 
         }
     }
     __syncthreads();
-    Tally<R> t = lepton_tally<R, SURR>(a.st);
+    Tally<R> t;
+    if constexpr (!SURR) t.max_p = max_p_before<R>(a.st);
     for (u64 i = (u64)blockIdx.x * kBlock + threadIdx.x; i < n; i += (u64)gridDim.x * kBlock) {
         const Lepton<R> p = load_lepton<R>(a, s, i);
         uint32_t N = lepton_nsub(a, s, i, p, t, a.dt);
@@ -1732,7 +1748,7 @@ __global__ __launch_bounds__(kBlock, SURR ? 2 : 3) void k_light(StepArgs a) {
     uint32_t *hist = hist_sh[wv];
     uint16_t *order = order_sh[wv];
     const u64 nwaves = (u64)gridDim.x * (kBlock / 64);
-    Tally<R> t = lepton_tally<R, SURR>(a.st);
+    Tally<R> t;
     for (u64 t0 = ((u64)blockIdx.x * (kBlock / 64) + wv) * tile; t0 < n; t0 += nwaves * tile) {
         hist[lane] = 0;
         __syncwarp();
@@ -1771,7 +1787,8 @@ __global__ __launch_bounds__(kBlock, SURR ? 2 : 3) void k_light(StepArgs a) {
         }
         __syncwarp();
     }
-    flush_children_block(L.cb, a.sp[2], a.seed, step_of(a));
+    flush_children_block(L.cb, a.sp[2], a.seed, step_of(a));   // begins with a barrier
+    if constexpr (!SURR) t.max_p = L.seen.get() / Draw<R>::kYScale;
     flush_tally(t, a.st, s);
 }
 
@@ -1808,7 +1825,7 @@ __global__ __launch_bounds__(kBlock, !SURR && sizeof(R) == 4 ? 3 : 2) void k_til
     uint32_t *nsub = nsub_sh[wv];
     uint16_t *rank = rank_sh[wv];   // within the slots of the same key
     const u64 nwaves = (u64)gridDim.x * (kBlock / 64);
-    Tally<R> t = lepton_tally<R, SURR>(a.st);
+    Tally<R> t;
     for (u64 t0 = ((u64)blockIdx.x * (kBlock / 64) + wv) * tile; t0 < n; t0 += nwaves * tile) {
         hist[lane] = 0;
         __syncwarp();
@@ -1849,7 +1866,8 @@ __global__ __launch_bounds__(kBlock, !SURR && sizeof(R) == 4 ? 3 : 2) void k_til
         }
         __syncwarp();
     }
-    flush_children_block(L.cb, a.sp[2], a.seed, step_of(a));
+    flush_children_block(L.cb, a.sp[2], a.seed, step_of(a));   // begins with a barrier
+    if constexpr (!SURR) t.max_p = L.seen.get() / Draw<R>::kYScale;
     flush_tally(t, a.st, s);
 }
 
@@ -1874,7 +1892,7 @@ __global__ __launch_bounds__(kBlock, SURR ? 2 : sizeof(R) == 4 ? 4 : 3) void k_h
     const uint32_t chunk = fair >= a.chunk ? a.chunk : (uint32_t)((fair + grain - 1) / grain * grain);
     if ((u64)blockIdx.x * (kBlock / 64) * chunk >= H) return;   // nor does the queue, which starts after these, hold any
     auto &cb = lepton_lds_init(a, L);
-    Tally<R> t = lepton_tally<R, SURR>(a.st);
+    Tally<R> t;
     // the first chunk of every wave is assigned statically; later ones are
     // claimed from the queue, which starts after all static chunks
     u64 base = first_lane(((u64)blockIdx.x * (kBlock / 64) + threadIdx.x / 64) * chunk);
@@ -1894,7 +1912,8 @@ __global__ __launch_bounds__(kBlock, SURR ? 2 : sizeof(R) == 4 ? 4 : 3) void k_h
         if (__lane_id() == 0) nb = nwaves * chunk + atomicAdd(&a.st->queue[s], (u64)chunk);
         base = first_lane(nb);
     }
-    flush_children_block(L.cb, a.sp[2], a.seed, step_of(a));
+    flush_children_block(L.cb, a.sp[2], a.seed, step_of(a));   // begins with a barrier
+    if constexpr (!SURR) t.max_p = L.seen.get() / Draw<R>::kYScale;
     flush_tally(t, a.st, s, 1);
 }
 
