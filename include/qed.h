@@ -287,7 +287,8 @@ typedef struct qed_tuning {
                                       particle the pre-pass did not finish goes through the
                                       queue, and the tile pass is not launched) */
     uint32_t chunk;                /* binned scheduler: queue entries a wave claims at once
-                                      (a multiple of 64, >= 64) */
+                                      (a multiple of 64, >= 64); a queue too short to give
+                                      every wave that many is dealt out evenly instead */
     uint32_t resolve_batch;        /* candidates (Algorithm 1) or emissions (surrogate sampler)
                                       a wave lets wait before it resolves them together
                                       (1..64; results do not depend on it) */
@@ -304,10 +305,11 @@ typedef struct qed_tuning {
     uint32_t bins_per_octave;      /* binned scheduler: sub-step-count bins per octave of N
                                       (4..32; the heavy queue is ordered by bin, so finer bins
                                       give the lanes of a wave closer counts) */
-    uint32_t light_tile;           /* binned scheduler: slots per wave tile of the light pass
-                                      (64..512, a multiple of 64) */
-    uint32_t tiled_slots;          /* tiled scheduler: slots per wave tile (64..256, a multiple
-                                      of 64) */
+    uint32_t light_tile;           /* binned scheduler: most slots per wave tile of the light
+                                      pass (64..512, a multiple of 64); few particles take
+                                      smaller tiles, so that more waves have one */
+    uint32_t tiled_slots;          /* tiled scheduler: most slots per wave tile (64..256, a
+                                      multiple of 64); smaller as for light_tile */
     uint32_t deposit_sort_min;     /* qed_deposit sorts the particles by grid tile (4^3 cells)
                                       and sums dense tiles in LDS when the species' capacity
                                       is at least this (0: always; 0xffffffff: never, every

@@ -29,8 +29,9 @@ FLAGS = [
     "-ffp-contract=on",
     # the machine-level loop-invariant pass hoists the literals of the double-precision
     # polynomials (pow, ln, exp) out of the particle loops into vector registers, which
-    # cost the streaming passes up to half of their waves: k_prepass<float> takes 70
-    # instead of 128 registers without it, k_lepton<float> 119 instead of 172
+    # costs waves or spills: within the registers that their launch bounds leave,
+    # k_prepass<float> would spill 152 bytes a lane and k_lepton<float> 304; without the pass
+    # they take 52 and 126 registers and spill none
     "-mllvm", "-disable-machine-licm",
     "-Wall", "-Wno-unused-function",
 ]

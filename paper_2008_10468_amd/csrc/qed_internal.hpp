@@ -100,13 +100,13 @@ struct StepArgs {
     uint32_t step, max_sub;
     int emission, pairs;   // which algorithms run in this step
     uint32_t light_max;    // binned scheduler: largest N handled by the light pass
-    uint32_t chunk;        // binned scheduler: queue entries claimed per wave (multiple of 64)
+    uint32_t chunk;        // binned scheduler: queue entries claimed per wave (multiple of 64; a short queue: its share)
     uint32_t resolve_batch;  // waiting candidates or emissions that trigger a batched resolve (1..64)
     uint32_t prepass_finish; // binned: the pre-pass finishes particles of one quiet sub-step
     uint32_t bins_per_octave; // binned: sub-step-count bins per octave (4..kMaxBinsPerOctave)
-    uint32_t light_tile;     // binned: slots per wave tile of the light pass (64..512, a multiple of 64)
+    uint32_t light_tile;     // binned: most slots per wave tile of the light pass (64..512, a multiple of 64)
     uint32_t tile_waves;     // light, tiled: waves a launch should reach before its tiles grow (8 per CU)
-    uint32_t tiled_slots;    // tiled: slots per wave tile (64..256, a multiple of 64)
+    uint32_t tiled_slots;    // tiled: most slots per wave tile (64..256, a multiple of 64)
     uint8_t *alive;        // photon flags, one per slot: 0 decayed, 1 alive
     u64 *dead_idx;         // slots of the photons that decayed this step
     u64 *hole_idx;         // compaction lists
