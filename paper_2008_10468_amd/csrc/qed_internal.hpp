@@ -156,8 +156,8 @@ enum KernelId {
 };
 
 // Blocks of k_prepass<float> that one compute unit holds at a time, without and with the
-// optical-depth path (more than 6 there squeeze its scalar registers: 430 to 450 us for
-// 16.8M electrons).
+// optical-depth path (16.8M electrons there: 423 us at 6, 428 held to the registers of 7 and
+// 434 to those of 8, each with its own grid).
 constexpr int kPrepassBlocks[2] = {8, 6};
 
 // Enqueue one kernel of a step (precision: 0 = F64, 1 = MIXED).  blocks is the
