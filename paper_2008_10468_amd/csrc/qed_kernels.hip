@@ -131,8 +131,8 @@ struct Tally {
 // rejects most candidates without evaluating their probability, but not those whose bound
 // lies above this one, so max_p is exact; it starts at what earlier passes have found, and
 // a block shares it, so that few are evaluated for it alone (us a pass without and with the exact
-// value: hot spot of 16.8M electrons 1756 and 1758, shower 1265 and 1271, 16,384 ring electrons
-// in FP64 149 and 151.5; held by every lane for itself, the hot spot took 1768).
+// value: hot spot of 16.8M electrons 1756 and 1762, shower 1262 and 1244, eight laser steps 1285
+// and 1284; held by every lane for itself, the hot spot took 1768).
 template <class R>
 struct MaxSeen {
     using Bits = typename std::conditional<sizeof(R) == 4, uint32_t, unsigned long long>::type;
@@ -143,6 +143,13 @@ struct MaxSeen {
         return fmax(p, __builtin_bit_cast(R, atomicMax(&bits, __builtin_bit_cast(Bits, p))));
     }
 };
+
+// The smaller of two non-negative values; floats by their bits, one instruction (fmin takes
+// three: it also quiets NaNs).
+__device__ __forceinline__ float lesser(float a, float b) {
+    return __builtin_bit_cast(float, min(__builtin_bit_cast(uint32_t, a), __builtin_bit_cast(uint32_t, b)));
+}
+__device__ __forceinline__ double lesser(double a, double b) { return fmin(a, b); }
 
 // max_p of the earlier passes.
 template <class R>
@@ -347,9 +354,11 @@ struct Draw<float> {
                                           uint32_t khi) {
         w = philox10(idlo, idhi, step, k >> 1, klo, khi);
     }
-    // of its first (half = 0) or second pair: the word of x, and y in units of 2^-24
+    // of its first (half = 0) or second pair: the word of x, and y in units of 2^-24 without the
+    // lowest bit that u24 sets (at most y: the squeeze lets a candidate more through, for one
+    // instruction less)
     __device__ __forceinline__ uint32_t xword(int half) const { return half ? w.z : w.x; }
-    __device__ __forceinline__ float test(int half) const { return (float)(((half ? w.w : w.y) >> 8) | 1u); }
+    __device__ __forceinline__ float test(int half) const { return (float)((half ? w.w : w.y) >> 8); }
     // the pair of sub-step k
     __device__ __forceinline__ void pair(uint32_t k, float &x, float &y) const {
         const bool odd = (k & 1u) != 0u;
@@ -758,7 +767,7 @@ __device__ __forceinline__ void lepton_loop(const StepArgs &a, int s, u64 i, uin
         push_substep<R, FK>(p, c.hex, c.hey, c.hez, c.hq, c.e2, c.str, ux, uy, uz, dx, dy, dz, rs, o, tl.guard);
         if constexpr (FK != 2) ab = accept_bound(kyb, o.chi, o.ig, at);
         ++k;
-        lim = accept_may((R)fmin(draw.test(half), seen), draw.xword(half), ab, at) ? 0u : N;
+        lim = accept_may(lesser(draw.test(half), seen), draw.xword(half), ab, at) ? 0u : N;
     };
     for (;;) {
         u64 mp;   // lanes that wait
@@ -1341,14 +1350,14 @@ struct LeptonLds<float, true> {
 
 template <class R>
 __device__ __forceinline__ ChildPool<R> &lepton_lds_init(const StepArgs &a, LeptonLds<R, false> &L) {
+    const R seen = max_p_before<R>(a.st) * Draw<R>::kYScale;   // under way with the tables
     if (threadIdx.x == 0) {
         L.cb.tail = L.cb.written[0] = L.cb.written[1] = L.cb.freed[0] = L.cb.freed[1] = 0;
         L.cb.dst = a.sp[2];
     }
     accept_stage(L.acc);
     syn_stage(L.tab);
-    if (threadIdx.x == 0)
-        L.seen.bits = __builtin_bit_cast(typename MaxSeen<R>::Bits, max_p_before<R>(a.st) * Draw<R>::kYScale);
+    if (threadIdx.x == 0) L.seen.bits = __builtin_bit_cast(typename MaxSeen<R>::Bits, seen);
     __syncthreads();
     return L.cb;
 }
@@ -1400,7 +1409,7 @@ __device__ __forceinline__ bool finish_single_fk(const StepArgs &a, int s, u64 i
     }
     draw.block(0u, (uint32_t)pid, (uint32_t)(pid >> 32), step_of(a), (uint32_t)a.seed, (uint32_t)(a.seed >> 32));
     const AcceptBound<R> ab = accept_bound(c.kcb * Draw<R>::kYScale, o.chi, o.ig, at);
-    if (accept_may((R)fmin(draw.test(0), tl.max_p * Draw<R>::kYScale), draw.xword(0), ab, at)) {
+    if (accept_may(lesser(draw.test(0), tl.max_p * Draw<R>::kYScale), draw.xword(0), ab, at)) {
         R x, y, x3, omx3;
         draw.pair(0u, x, y);
         const R pm = accept_prob(c.kcb, o.chi, o.ig, x, tab, x3, omx3);
