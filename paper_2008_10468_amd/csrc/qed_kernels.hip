@@ -130,9 +130,10 @@ struct Tally {
 // The largest acceptance probability so far, in units of 1 / Draw::kYScale.  Algorithm 1
 // rejects most candidates without evaluating their probability, but not those whose bound
 // lies above this one, so max_p is exact; it starts at what earlier passes have found, and
-// a block shares it, so that few are evaluated for it alone (us a pass without and with the exact
-// value: hot spot of 16.8M electrons 1756 and 1762, shower 1262 and 1244, eight laser steps 1285
-// and 1284; held by every lane for itself, the hot spot took 1768).
+// a block shares it, so that few are evaluated for it alone (us without and with the exact value:
+// a pass of the hot spot of 16.8M electrons 1756 and 1762, of a shower 1262 and 1246, eight laser
+// steps 1277 and 1281, k_lepton<double> on 16,384 ring electrons 56.2 and 57.7; held by
+// every lane for itself, the hot spot took 1768).
 template <class R>
 struct MaxSeen {
     using Bits = typename std::conditional<sizeof(R) == 4, uint32_t, unsigned long long>::type;
@@ -144,12 +145,11 @@ struct MaxSeen {
     }
 };
 
-// The smaller of two non-negative values; floats by their bits, one instruction (fmin takes
-// three: it also quiets NaNs).
+// The smaller of two non-negative values by their bits, one instruction (fmin takes three: it
+// also quiets NaNs).
 __device__ __forceinline__ float lesser(float a, float b) {
     return __builtin_bit_cast(float, min(__builtin_bit_cast(uint32_t, a), __builtin_bit_cast(uint32_t, b)));
 }
-__device__ __forceinline__ double lesser(double a, double b) { return fmin(a, b); }
 
 // max_p of the earlier passes.
 template <class R>
@@ -348,15 +348,15 @@ struct Draw;
 template <>
 struct Draw<float> {
     u32x4 w;
-    static constexpr float kYScale = 0x1p+24f;   // test() over y
+    static constexpr float kYScale = 0x1p+24f;   // of test()
     // the block that holds sub-step k
     __device__ __forceinline__ void block(uint32_t k, uint32_t idlo, uint32_t idhi, uint32_t step, uint32_t klo,
                                           uint32_t khi) {
         w = philox10(idlo, idhi, step, k >> 1, klo, khi);
     }
-    // of its first (half = 0) or second pair: the word of x, and y in units of 2^-24 without the
-    // lowest bit that u24 sets (at most y: the squeeze lets a candidate more through, for one
-    // instruction less)
+    // of its first (half = 0) or second pair: the word of x, and for the squeeze the top 24 bits
+    // of y's word, at most kYScale y (fewer instructions than y itself; a candidate more
+    // passes where they differ)
     __device__ __forceinline__ uint32_t xword(int half) const { return half ? w.z : w.x; }
     __device__ __forceinline__ float test(int half) const { return (float)((half ? w.w : w.y) >> 8); }
     // the pair of sub-step k
@@ -375,13 +375,13 @@ struct Draw<float> {
 template <>
 struct Draw<double> {
     u32x4 w;
-    static constexpr double kYScale = 1.0;
+    static constexpr double kYScale = 0x1p+24;
     __device__ __forceinline__ void block(uint32_t k, uint32_t idlo, uint32_t idhi, uint32_t step, uint32_t klo,
                                           uint32_t khi) {
         w = philox10(idlo, idhi, step, k, klo, khi);
     }
     __device__ __forceinline__ uint32_t xword(int) const { return w.x; }
-    __device__ __forceinline__ double test(int) const { return u53(w.z, w.w); }
+    __device__ __forceinline__ float test(int) const { return (float)(w.z >> 8); }
     __device__ __forceinline__ void pair(uint32_t, double &x, double &y) const {
         x = u53(w.x, w.y);
         y = u53(w.z, w.w);
@@ -748,7 +748,7 @@ __device__ __forceinline__ void lepton_loop(const StepArgs &a, int s, u64 i, uin
     const uint32_t step = step_of(a);
     const int batch = (int)a.resolve_batch;
     const R kyb = c.kcb * Draw<R>::kYScale;
-    R seen = ms.get();
+    float seen = (float)ms.get();   // the bound's margin covers its rounding
     R ux = p.ux, uy = p.uy, uz = p.uz;
     R dx = 0, dy = 0, dz = 0;
     uint32_t nev = 0;
@@ -767,7 +767,7 @@ __device__ __forceinline__ void lepton_loop(const StepArgs &a, int s, u64 i, uin
         push_substep<R, FK>(p, c.hex, c.hey, c.hez, c.hq, c.e2, c.str, ux, uy, uz, dx, dy, dz, rs, o, tl.guard);
         if constexpr (FK != 2) ab = accept_bound(kyb, o.chi, o.ig, at);
         ++k;
-        lim = accept_may(lesser(draw.test(half), seen), draw.xword(half), ab, at) ? 0u : N;
+        lim = accept_may((R)lesser(draw.test(half), seen), draw.xword(half), ab, at) ? 0u : N;
     };
     for (;;) {
         u64 mp;   // lanes that wait
@@ -797,7 +797,7 @@ __device__ __forceinline__ void lepton_loop(const StepArgs &a, int s, u64 i, uin
             R x, y;
             draw.pair(k - 1u, x, y);
             const R pm = accept_prob(c.kcb, o.chi, o.ig, x, tab, x3, omx3);
-            if (pm * Draw<R>::kYScale > seen) seen = ms.raise(pm * Draw<R>::kYScale);
+            if (pm * Draw<R>::kYScale > (R)seen) seen = (float)ms.raise(pm * Draw<R>::kYScale);
             tl.clips += pm > R(1);
             acc = y < pm;
             lim = N;
@@ -1409,7 +1409,7 @@ __device__ __forceinline__ bool finish_single_fk(const StepArgs &a, int s, u64 i
     }
     draw.block(0u, (uint32_t)pid, (uint32_t)(pid >> 32), step_of(a), (uint32_t)a.seed, (uint32_t)(a.seed >> 32));
     const AcceptBound<R> ab = accept_bound(c.kcb * Draw<R>::kYScale, o.chi, o.ig, at);
-    if (accept_may(lesser(draw.test(0), tl.max_p * Draw<R>::kYScale), draw.xword(0), ab, at)) {
+    if (accept_may((R)lesser(draw.test(0), (float)(tl.max_p * Draw<R>::kYScale)), draw.xword(0), ab, at)) {
         R x, y, x3, omx3;
         draw.pair(0u, x, y);
         const R pm = accept_prob(c.kcb, o.chi, o.ig, x, tab, x3, omx3);
